@@ -1,11 +1,37 @@
 // attn_f32.hip -- the fp32 member of the attention family: the same rows,
-// segments and causal offset as the bf16 kernel, computed entirely in fp32 on
-// the vector ALUs (no reduced-precision matrix instructions), for inputs whose
+// segments and causal offset as the 16-bit kernels, computed entirely in fp32
+// (fp32 matrix instructions, no reduced precision anywhere), for inputs whose
 // tolerance is 1e-5.
 //
-// Workgroup: 64 query rows x 4 lanes per row; each lane owns a quarter of the
-// head dim of its row (q and the output accumulator live in registers).  Key
-// tiles of 32 rows are staged in LDS and read by every row of the workgroup.
+// What bounds it: the fp32 matrix rate, 256 flops per clock and CU.  A
+// workgroup is 8 waves (two per SIMD) that all hold the same 16 * NCT query
+// rows and split the keys: wave w takes the 16-key stages w, w + 8, ... of the
+// tile's keys, straight from memory into registers (a K or V row reaches its
+// lanes in 16-byte pieces; the next stage's pieces are requested as the current
+// ones are used up), so the key loop has no barrier and no LDS.  The eight
+// (m, l, O) meet in LDS at the end.
+//
+// Transposed products as in the 16-bit kernels, on v_mfma_f32_16x16x4_f32
+// (lane l: column l % 16, k group kg = l / 16):
+//   S^T[key][row] = K Q^T     lane (key, kg) reads head dims 16c + 4 kg .. +3 of
+//                             its key; product e of chunk c uses dim 16c + 4 kg + e
+//   O^T[d][row] += V^T P^T    the score accumulator register e of a lane is the
+//                             weight of key 4 kg + e: the operand of product e as
+//                             it stands; lane (m, kg) reads dims MT m .. MT m + MT - 1
+//                             of key 4 kg + e, MT = D / 16
+//
+// Row tiles: 16 rows (NCT = 1) give twice the workgroups, 32 rows (NCT = 2) read
+// every key once for two column tiles; the caller takes 32 once there are 512 of
+// them (two rounds of the part).
+//
+// Measured against the vector-ALU kernel this one replaces (64 rows per
+// workgroup, the keys one after another), 32 / 8 heads, d = 128: 24 tokens over
+// 945 cached rows 438 -> 27.7 us (48 workgroups: the bound is their own 14 us of
+// matrix time), prefill 1000 491 -> 112 us, 4000 4257 -> 1274 us (103 TFLOP/s of
+// the 157 peak); one token over 700 rows 372 -> 24 us.  Error against 64 bits at
+// the first shape: 7.4e-7 -> 3.3e-7 (2-norm).
+#include <type_traits>
+
 #include "attn_common.hpp"
 
 namespace kvr {
@@ -13,10 +39,11 @@ namespace {
 
 using dev::rope_rot;
 
-constexpr int ROWS = kRowsF32;
-constexpr int LANES_PER_ROW = 4;
-constexpr int THREADS = ROWS * LANES_PER_ROW;
-constexpr int KT = 32;   // keys per LDS tile
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int NW = 8;              // waves per workgroup
+constexpr int THREADS = 64 * NW;
+constexpr int SK = 16;             // keys per stage
 
 __device__ __forceinline__ int find_segment_f32(const AttnParams &p, int tile) {
     int lo = 0, hi = p.n_seg - 1;
@@ -27,14 +54,31 @@ __device__ __forceinline__ int find_segment_f32(const AttnParams &p, int tile) {
     return lo;
 }
 
-template <int D>
+// the four lanes l, l^16, l^32, l^48 of a query row
+__device__ __forceinline__ float row_max(float x) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return dev::pair_max(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
+}
+__device__ __forceinline__ float row_sum(float x) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return dev::pair_sum(__uint_as_float(a[0]) + __uint_as_float(a[1]));
+}
+
+template <int D, int NCT>
 __global__ __launch_bounds__(THREADS) void attn_f32_kernel(const AttnParams p) {
-    constexpr int DQ = D / LANES_PER_ROW;   // head-dim slice per lane
-    __shared__ __attribute__((aligned(16))) float ks[KT][D];
-    __shared__ __attribute__((aligned(16))) float vs[KT][D];
+    constexpr int ROWS = 16 * NCT;
+    constexpr int NC = D / 16;         // 16-byte pieces of a K row per lane
+    constexpr int MT = D / 16;         // 16-row tiles of O^T
+    constexpr int Q4 = MT / 4;         // 16-byte pieces of a V row per lane
+    constexpr int UNITS = MT * NCT;    // (column tile, 16-byte piece of O) pairs of the merge
+    __shared__ float4 obuf[NW][UNITS][64];
+    __shared__ float mbuf[NW][NCT][16], lbuf[NW][NCT][16];
 
     const int tid = threadIdx.x;
-    const int part = tid % LANES_PER_ROW;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+    const int j = lane & 15;
+    const int kg = lane >> 4;
 
     int b = blockIdx.x;
     const int g = b % p.n_kv_heads;
@@ -49,113 +93,213 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(const AttnParams p) {
     const int row0 = rt * ROWS;
     const int row_last = min(row0 + ROWS, R) - 1;
     const int64_t npre = p.n_prefix;
+    const int64_t ke = npre + row_last / G + 1;     // keys any row here may see
+    const int64_t k_full = npre + row0 / G + 1;     // keys every row here sees
+    const int nst = (int)((ke + SK - 1) / SK);
 
-    const int r = row0 + tid / LANES_PER_ROW;
-    const bool valid = r < R;
-    const int tok = valid ? r / G : 0;
-    const int head = g * G + (valid ? r % G : 0);
-    const int64_t pos = valid ? npre + tok : -1;
-    const int64_t ke = npre + row_last / G + 1;
-
-    float q[DQ], o[DQ];
-    {
-        const float *qrow = (const float *)p.q + ((int64_t)(tok0 + tok) * p.n_q_heads + head) * D + part * DQ;
+    bool valid[NCT];
+    int tok[NCT], head[NCT];
+    int64_t pos[NCT];
+    f32x4 q[NCT][NC], o[NCT][MT];
+    float m_run[NCT], l_run[NCT];
 #pragma unroll
-        for (int c = 0; c < DQ; ++c) {
-            q[c] = valid ? qrow[c] : 0.f;
-            o[c] = 0.f;
-        }
-        // RoPE (prefill, readers): dim i < D/2 of the row pairs with dim
-        // i + D/2, which the lane two over (part + 2) holds
-        if (p.rope) {
-            const int half = part & 1;              // which DQ-slice of the pair index
-            const bool upper = part >= 2;
-            const float *cs = p.rope + (valid ? pos : 0) * D + 2 * half * DQ;
+    for (int c = 0; c < NCT; ++c) {
+        const int r = row0 + 16 * c + j;
+        valid[c] = r < R;
+        tok[c] = valid[c] ? r / G : 0;
+        head[c] = g * G + (valid[c] ? r % G : 0);
+        pos[c] = valid[c] ? npre + tok[c] : -1;
+        m_run[c] = -INFINITY;
+        l_run[c] = 0.f;
 #pragma unroll
-            for (int c = 0; c < DQ; ++c) {
-                const float other = __shfl_xor(q[c], 2);
-                float y1, y2;
-                if (upper) rope_rot(other, q[c], cs[2 * c], cs[2 * c + 1], y1, y2);
-                else rope_rot(q[c], other, cs[2 * c], cs[2 * c + 1], y1, y2);
-                if (valid) q[c] = upper ? y2 : y1;
-            }
+        for (int mt = 0; mt < MT; ++mt) o[c][mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        const float *qrow = (const float *)p.q + ((int64_t)(tok0 + tok[c]) * p.n_q_heads + head[c]) * D + 4 * kg;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) q[c][i] = valid[c] ? *(const f32x4 *)(qrow + 16 * i) : (f32x4){0.f, 0.f, 0.f, 0.f};
+        // RoPE (prefill, readers): dim i < D/2 pairs with dim i + D/2, which the
+        // same lane holds NC/2 pieces further
+        if (p.rope && valid[c]) {
+            const float *cs = p.rope + pos[c] * D + 8 * kg;
+#pragma unroll
+            for (int i = 0; i < NC / 2; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float y1, y2;
+                    rope_rot(q[c][i][e], q[c][i + NC / 2][e], cs[32 * i + 2 * e], cs[32 * i + 2 * e + 1], y1, y2);
+                    q[c][i][e] = y1;
+                    q[c][i + NC / 2][e] = y2;
+                }
         }
     }
-    float m_run = -INFINITY, l_run = 0.f;
-    const float scale = p.scale;
 
+    // log2 domain: 2^(s - m) with s the product times scale * log2(e)
+    const float c2 = p.scale_log2;
     const float *kc = (const float *)p.kc + (int64_t)g * p.cap * D;
     const float *vc = (const float *)p.vc + (int64_t)g * p.cap * D;
     const int64_t nstride = p.new_tok_stride;
     const float *kn = (const float *)p.kn + (int64_t)tok0 * nstride + p.new_head_stride * g;
     const float *vn = (const float *)p.vn + (int64_t)tok0 * nstride + p.new_head_stride * g;
+    // row of a key; keys past the end repeat the last one (masked, and their V
+    // pieces zeroed before use)
+    auto row = [&](const float *cache, const float *fresh, int64_t key) {
+        const int64_t k = key < ke ? key : ke - 1;
+        return k < npre ? cache + k * D : fresh + (k - npre) * nstride;
+    };
 
-    for (int64_t k0 = 0; k0 < ke; k0 += KT) {
-        // stage KT key rows: float4 chunks, D/4 per row
-        for (int idx = tid; idx < KT * (D / 4); idx += THREADS) {
-            const int kr = idx / (D / 4);
-            const int c4 = idx % (D / 4);
-            const int64_t key = k0 + kr;
-            float4 kv = make_float4(0.f, 0.f, 0.f, 0.f), vv = kv;
-            if (key < ke) {
-                const float *ksrc = key < npre ? kc + key * D : kn + (key - npre) * nstride;
-                const float *vsrc = key < npre ? vc + key * D : vn + (key - npre) * nstride;
-                kv = *(const float4 *)(ksrc + 4 * c4);
-                vv = *(const float4 *)(vsrc + 4 * c4);
-            }
-            *(float4 *)&ks[kr][4 * c4] = kv;
-            *(float4 *)&vs[kr][4 * c4] = vv;
-        }
-        __syncthreads();
+    f32x4 kf[NC], vf[4][Q4];
+    const float *kp;
+    const float *vp[4];
+    auto point = [&](int t) {                       // this lane's rows of stage t
+        const int64_t key0 = (int64_t)t * SK;
+        kp = row(kc, kn, key0 + j) + 4 * kg;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) vp[e] = row(vc, vn, key0 + 4 * kg + e) + MT * j;
+    };
+    auto kload = [&](int i) { kf[i] = *(const f32x4 *)(kp + 16 * i); };
+    auto vload = [&](int e, int h) { vf[e][h] = *(const f32x4 *)(vp[e] + 4 * h); };
 
-        float s[KT];
-        float mx = -INFINITY;
+    // one stage; `more`: request stage t + NW's pieces as this one's are used up
+    auto stage = [&](int t, auto more_tag) {
+        constexpr bool more = decltype(more_tag)::value;
+        const int64_t key0 = (int64_t)t * SK;
+        f32x4 s0[NCT], s1[NCT];
 #pragma unroll
-        for (int kk = 0; kk < KT; ++kk) {
-            float acc = 0.f;
+        for (int c = 0; c < NCT; ++c) s0[c] = s1[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        if constexpr (more) point(t + NW);
 #pragma unroll
-            for (int c = 0; c < DQ; ++c) acc = __builtin_fmaf(q[c], ks[kk][part * DQ + c], acc);
-            // the four lanes of a row hold the four quarter sums; all end with the same total
-            acc += __shfl_xor(acc, 1);
-            acc += __shfl_xor(acc, 2);
-            const int64_t key = k0 + kk;
-            s[kk] = key <= pos ? acc * scale : -INFINITY;
-            mx = fmaxf(mx, s[kk]);
-        }
-        const float m_new = fmaxf(m_run, mx);
-        if (m_new != -INFINITY) {
-            const float alpha = expf(m_run - m_new);   // 0 on the first visible tile
-            l_run *= alpha;
+        for (int i = 0; i < NC; ++i) {
 #pragma unroll
-            for (int c = 0; c < DQ; ++c) o[c] *= alpha;
-#pragma unroll
-            for (int kk = 0; kk < KT; ++kk) {
-                const float w = expf(s[kk] - m_new);
-                l_run += w;
-#pragma unroll
-                for (int c = 0; c < DQ; ++c) o[c] = __builtin_fmaf(w, vs[kk][part * DQ + c], o[c]);
+            for (int c = 0; c < NCT; ++c) {
+                s0[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][0], q[c][i][0], s0[c], 0, 0, 0);
+                s1[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][1], q[c][i][1], s1[c], 0, 0, 0);
+                s0[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][2], q[c][i][2], s0[c], 0, 0, 0);
+                s1[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][3], q[c][i][3], s1[c], 0, 0, 0);
             }
-            m_run = m_new;
+            if constexpr (more) kload(i);
         }
-        __syncthreads();
+        const bool masked = key0 + SK > k_full;
+        float w[NCT][4];
+#pragma unroll
+        for (int c = 0; c < NCT; ++c) {
+#pragma clang fp contract(off)
+            // the product is rounded before m is taken off, so that the largest
+            // score's weight is exactly 1 however large the scores are
+            float mx = -INFINITY;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float s = (s0[c][e] + s1[c][e]) * c2;
+                w[c][e] = masked && key0 + 4 * kg + e > pos[c] ? -INFINITY : s;
+                mx = fmaxf(mx, w[c][e]);
+            }
+            const float m_new = fmaxf(m_run[c], row_max(mx));
+            const float m_use = m_new == -INFINITY ? 0.f : m_new;   // nothing visible so far
+            const float alpha = __builtin_amdgcn_exp2f(m_run[c] - m_use);
+            m_run[c] = m_new;
+            float sum = 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                w[c][e] = __builtin_amdgcn_exp2f(w[c][e] - m_use);
+                sum += w[c][e];
+            }
+            if (__ballot(alpha != 1.f)) {
+                l_run[c] *= alpha;
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) o[c][mt][i] *= alpha;
+            }
+            l_run[c] += sum;
+        }
+        if (key0 + SK > ke) {                       // ragged end: no key there (0 * its repeated row)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (key0 + 4 * kg + e >= ke)
+#pragma unroll
+                    for (int h = 0; h < Q4; ++h) vf[e][h] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int c = 0; c < NCT; ++c)
+                    o[c][mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[e][mt / 4][mt % 4], w[c][e], o[c][mt], 0, 0, 0);
+            if constexpr (more) {
+#pragma unroll
+                for (int h = 0; h < Q4; ++h) vload(e, h);
+            }
+        }
+    };
+
+    if (wave < nst) {
+        point(wave);
+#pragma unroll
+        for (int i = 0; i < NC; ++i) kload(i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int h = 0; h < Q4; ++h) vload(e, h);
+        int t = wave;
+        for (; t + NW < nst; t += NW) stage(t, std::true_type{});
+        stage(t, std::false_type{});
     }
 
-    if (!valid) return;
-    const float inv = 1.f / l_run;
-    float *orow = (float *)p.out + ((int64_t)(tok0 + tok) * p.n_q_heads + head) * D + part * DQ;
+    // ---- the eight waves' (m, l, O): lane (row j, kg) holds O dims
+    // MT (4 kg + i) + mt, posted in pieces of four dims; unit u = (column tile,
+    // piece) is summed by wave u % 8 over the waves in order, scaled to the
+    // common maximum, and stored
 #pragma unroll
-    for (int c = 0; c < DQ; c += 4)
-        *(float4 *)(orow + c) = make_float4(o[c] * inv, o[c + 1] * inv, o[c + 2] * inv, o[c + 3] * inv);
+    for (int c = 0; c < NCT; ++c) {
+        const float l = row_sum(l_run[c]);
+        if (kg == 0) {
+            mbuf[wave][c][j] = m_run[c];
+            lbuf[wave][c][j] = l;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int h = 0; h < Q4; ++h)
+                obuf[wave][c * MT + i * Q4 + h][lane] =
+                    make_float4(o[c][4 * h][i], o[c][4 * h + 1][i], o[c][4 * h + 2][i], o[c][4 * h + 3][i]);
+    }
+    __syncthreads();
+    for (int u = wave; u < UNITS; u += NW) {
+        const int c = u / MT, piece = u % MT;
+        float M = -INFINITY;
+#pragma unroll
+        for (int x = 0; x < NW; ++x) M = fmaxf(M, mbuf[x][c][j]);
+        float l = 0.f;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int x = 0; x < NW; ++x) {
+            const float mx = mbuf[x][c][j];
+            const float a = mx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mx - M);   // a wave without keys
+            const float4 v = obuf[x][u][lane];
+            l = __builtin_fmaf(a, lbuf[x][c][j], l);
+            acc[0] = __builtin_fmaf(a, v.x, acc[0]);
+            acc[1] = __builtin_fmaf(a, v.y, acc[1]);
+            acc[2] = __builtin_fmaf(a, v.z, acc[2]);
+            acc[3] = __builtin_fmaf(a, v.w, acc[3]);
+        }
+        const int r = row0 + 16 * c + j;
+        if (r >= R) continue;
+        const float inv = 1.f / l;
+        float *orow = (float *)p.out + ((int64_t)(tok0 + r / G) * p.n_q_heads + g * G + r % G) * D;
+        *(float4 *)(orow + MT * 4 * kg + 4 * piece) = make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
+    }
+}
+
+template <int D>
+hipError_t launch_d(const AttnParams &p, int grid, hipStream_t s) {
+    if (p.row_tile == 16) hipLaunchKernelGGL((attn_f32_kernel<D, 1>), dim3(grid), dim3(THREADS), 0, s, p);
+    else hipLaunchKernelGGL((attn_f32_kernel<D, 2>), dim3(grid), dim3(THREADS), 0, s, p);
+    return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_attn_f32(const AttnParams &p, int head_dim, int grid, hipStream_t s) {
-    if (head_dim == 128)
-        hipLaunchKernelGGL(attn_f32_kernel<128>, dim3(grid), dim3(THREADS), 0, s, p);
-    else
-        hipLaunchKernelGGL(attn_f32_kernel<64>, dim3(grid), dim3(THREADS), 0, s, p);
-    return hipGetLastError();
+    return head_dim == 128 ? launch_d<128>(p, grid, s) : launch_d<64>(p, grid, s);
 }
 
 }  // namespace kvr

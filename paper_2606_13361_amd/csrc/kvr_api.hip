@@ -32,6 +32,8 @@ constexpr int64_t kRowsSplitMaxKeys = 640;
 // kReaderMergeCost, and the fp32 partials written and read back at about
 // kPartialBytesPerUs.
 constexpr int64_t kCus = 256;
+// fp32: 32-row tiles from this many on
+constexpr int64_t kF32WideTiles = 2 * kCus;
 constexpr int64_t kReaderMaxSplits = 16;
 constexpr int64_t kReaderMinSplitTiles = 4;
 constexpr double kReaderSplitFixed = 0.07;
@@ -70,7 +72,13 @@ float eff_scale(const kvr_desc *d) { return d->scale > 0.f ? d->scale : 1.f / sq
 
 int elt_bytes(const kvr_desc *d) { return is16(d) ? 2 : 4; }
 
-int rows_per_tile(const kvr_desc *d) { return is16(d) ? kRowsBf16 : kRowsF32; }
+// Query rows per workgroup for a call of `rows` query rows per kv head.  fp32: 32
+// rows read each key once for two column tiles, 16 give twice the workgroups;
+// 32 pays once those fill the part twice over.
+int rows_per_tile(const kvr_desc *d, int64_t rows) {
+    if (is16(d)) return kRowsBf16;
+    return rows / kRowsF32 * d->n_kv_heads >= kF32WideTiles ? kRowsF32 : kRowsF32 / 2;
+}
 
 struct Split {
     int32_t nsplit;
@@ -274,7 +282,8 @@ int launch_single(const kvr_desc *d, int mode, const void *Q, const void *K, con
     const int64_t G = p.group;
     const int64_t rows = G * n_tok;
     if (rows > 0x7fffffff) return KVR_ERR_SHAPE;   // row indices are 32-bit on the device
-    const int rpt = rows_per_tile(d);
+    const int rpt = rows_per_tile(d, rows);
+    p.row_tile = rpt;
     const int64_t tiles = (rows + rpt - 1) / rpt;
     p.n_seg = 1;
     p.reverse = reverse ? 1 : 0;
@@ -382,7 +391,7 @@ int batched_impl(const kvr_desc *desc, const void *Qs, const void *Ks, const voi
                  const float *rope, void *ws, void *stream) {
     const int64_t G = desc->n_q_heads / desc->n_kv_heads;
     const bool pp = use_pp(desc);
-    const int rpt = pp ? kRowsPP : rows_per_tile(desc);
+    const int rpt = pp ? kRowsPP : rows_per_tile(desc, G * cu[n]);
     for (int32_t first = 0; first < n; first += kMaxSegments) {
         const int32_t cnt = (n - first) < kMaxSegments ? (n - first) : kMaxSegments;
         AttnParams p;
@@ -391,6 +400,7 @@ int batched_impl(const kvr_desc *desc, const void *Qs, const void *Ks, const voi
         p.rope = rope;
         p.n_prefix = L_prefix;
         p.reverse = 0;
+        p.row_tile = rpt;
         int32_t tiles = 0, seg = 0;
         for (int32_t i = 0; i < cnt; ++i) {
             const int64_t len = cu[first + i + 1] - cu[first + i];

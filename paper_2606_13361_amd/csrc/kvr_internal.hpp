@@ -53,6 +53,7 @@ struct AttnParams {
     // many readers on the two-group kernel: row tiles from this one on run as
     // nsplit key splits each (tiles_total: none)
     int32_t tail_tile0;
+    int32_t row_tile;    // fp32 path: query rows per workgroup, 16 or 32
     int32_t seg_tok0[kMaxSegments + 1];   // packed token offset of each segment (cu_seqlens)
     int32_t seg_tile0[kMaxSegments + 1];  // first row tile of each segment (prefix sums; not used
                                           // by the two-group kernel, whose reader tiles are packed)
@@ -134,7 +135,7 @@ hipError_t launch_rope_table(float *cs, int head_dim, double base, int64_t n_pos
 
 // row-tile geometry of the two paths
 constexpr int kRowsBf16 = 128;  // query rows per workgroup, bf16 path
-constexpr int kRowsF32 = 64;    // query rows per workgroup, fp32 path
+constexpr int kRowsF32 = 32;    // query rows per workgroup, fp32 path (16 when those are few)
 constexpr int kKeyTile = 64;    // keys per tile (split chunks are multiples of it)
 constexpr int kMaxSplits = 256; // key splits of one continuation (merge kernel LDS table)
 
