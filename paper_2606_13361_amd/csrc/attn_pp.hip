@@ -1,5 +1,5 @@
-// attn_pp.hip -- prefill and many readers, bf16, head_dim 128: the two-group
-// ("ping-pong") member of the attention family.
+// attn_pp.hip -- prefill, many readers and long continuations (one reader),
+// bf16, head_dim 128: the two-group ("ping-pong") member of the attention family.
 //
 // A workgroup is 8 waves, 2 per SIMD, holding 256 query rows of one kv head
 // (32 rows per wave, GQA-packed as everywhere in the family).  Waves 0-3 form

@@ -39,6 +39,12 @@ constexpr int64_t kReaderMinSplitTiles = 4;
 constexpr double kReaderSplitFixed = 0.07;
 constexpr double kReaderMergeCost = 0.04;
 constexpr double kReaderTileUs = 2.0;
+// A long continuation on the same kernel: from this many query rows per kv head
+// on in any case; fixed time of a workgroup and of the merge launch
+constexpr int64_t kLongRows = 8 * kRowsPP;
+constexpr int64_t kLongSplits = 48;
+constexpr double kLongSplitFixedUs = 6.0;
+constexpr double kLongMergeUs = 5.0;
 constexpr double kPartialBytesPerUs = 5.0e6;
 
 // bf16 and fp16 share the 16-bit MFMA path; f16() picks the element format
@@ -172,6 +178,61 @@ ReaderPlan plan_readers(const kvr_desc *d, int64_t L_prefix, int64_t total_S, in
     r.tail0 = r.tiles - tail;
     r.rows_tail = rows_tail;
     r.ws_bytes = (size_t)ns * d->n_kv_heads * r.rows_tail * (d->head_dim + 2) * sizeof(float);
+    return r;
+}
+
+// Continuations of more than kContMaxRows query rows per kv head (16-bit,
+// head_dim 128): the two-group kernel, as one reader, or the register-staged
+// one.  Per workgroup the two-group kernel is the faster one (256 rows and a
+// 64-key tile in about 1.7 us, the staged one 2 x 128 rows in about 1.8 us with
+// its last round only part full), but it starts slower (about 10 us of launch,
+// query rows and first tiles) and idles the waves of a partial row tile.  It
+// pays from eight full row tiles per kv head on over a prefix of at least four
+// key tiles, and below that where the staged plan needs a second round of
+// workgroups or so many splits that its merge takes several passes.  Measured, staged ->
+// two-group, 8 kv heads, 4 query heads each: 517 tokens over 7001 129.8 -> 87.5
+// us, 512 over 300 36.0 -> 31.6, 1024 over 1000 71.7 -> 61.0, 2000 over 1000 165
+// -> 87, 300 over 20000 (560 workgroups staged) 188 -> 115, 32 over 20000 (63
+// splits) 40.8 -> 32.9; beyond the line: 600 over 64 22.5 -> 25.6, 256 over 3774
+// 33.8 -> 36.2, 64 over 3774 19.7 -> 26.2, 32 over 9000 (36 splits) 24.5 -> 24.8.
+bool use_pp_long(const kvr_desc *d, int64_t L_prefix, int64_t S, const Split &sp) {
+    const int64_t rows = (int64_t)(d->n_q_heads / d->n_kv_heads) * S;
+    if (!use_pp(d) || rows <= kContMaxRows || L_prefix + S >= ((int64_t)1 << 30)) return false;   // 32-bit keys there
+    const int64_t staged = (rows + kRowsBf16 - 1) / kRowsBf16 * d->n_kv_heads * sp.nsplit;
+    return (rows >= kLongRows && L_prefix >= kReaderMinSplitTiles * kKeyTile) ||
+           (sp.nsplit > 1 && staged > kTargetWorkgroupsStaged) || sp.nsplit > kLongSplits;
+}
+// Its plan: row tiles of kRowsPP rows; fewer workgroups than compute units are
+// split over the keys, all alike.  The partials stay within ws_bytes, what
+// plan_split asked the caller for; the split count is the cheapest within that,
+// costs as for the readers.
+ReaderPlan plan_long(const kvr_desc *d, int64_t L_prefix, int64_t S, size_t ws_bytes) {
+    const int64_t G = d->n_q_heads / d->n_kv_heads;
+    const int64_t rows = G * S;
+    ReaderPlan r{(rows + kRowsPP - 1) / kRowsPP, 0, 1, 0, 0};
+    r.tail0 = r.tiles;
+    const int64_t wgs = r.tiles * d->n_kv_heads;
+    if (wgs >= kCus) return r;
+    const int64_t rec_bytes = d->n_kv_heads * rows * (d->head_dim + 2) * (int64_t)sizeof(float);
+    const int64_t by_keys = L_prefix / (kReaderMinSplitTiles * kKeyTile);
+    const int64_t by_ws = (int64_t)(ws_bytes / (size_t)rec_bytes);
+    const double wg_us = kReaderTileUs * (double)(L_prefix / kKeyTile + 2);
+    const double fixed = kLongSplitFixedUs / wg_us;
+    double best = 1.0 + fixed;
+    int64_t ns = 1;
+    for (int64_t k = 2; k <= kMaxSplits && k <= by_keys && k <= by_ws; ++k) {
+        const int64_t rounds = (wgs * k + kCus - 1) / kCus;
+        const double traffic = 2.0 * (double)k * (double)rec_bytes / kPartialBytesPerUs / wg_us;
+        const double c = (double)rounds * (1.0 / (double)k + fixed) + kLongMergeUs / wg_us + traffic;
+        if (c < best - 1e-9) {
+            best = c;
+            ns = k;
+        }
+    }
+    if (ns < 2) return r;
+    r.nsplit = ns;
+    r.tail0 = 0;
+    r.rows_tail = rows;
     return r;
 }
 
@@ -319,6 +380,14 @@ int launch_single(const kvr_desc *d, int mode, const void *Q, const void *K, con
         const int64_t pp_tiles = (rows + kRowsPP - 1) / kRowsPP;
         p.tiles_total = (int32_t)pp_tiles;
         e = launch_attn_pp(p, kModePrefill, f16(d), (int)(pp_tiles * p.n_kv_heads), stream);
+    } else if (mode == kModeContinue && use_pp_long(d, n_prefix, n_tok, sp)) {
+        const ReaderPlan lp = plan_long(d, n_prefix, n_tok, sp.ws_bytes);
+        p.tiles_total = (int32_t)lp.tiles;
+        p.tail_tile0 = (int32_t)lp.tail0;
+        p.nsplit = (int32_t)lp.nsplit;
+        p.rows_total = (int32_t)lp.rows_tail;
+        e = launch_attn_pp(p, kModeContinue, f16(d),
+                           (int)((lp.tail0 + (lp.tiles - lp.tail0) * lp.nsplit) * p.n_kv_heads), stream);
     } else if (is16(d)) {
         e = launch_attn_bf16(p, d->head_dim, mode, f16(d), (int)grid, stream);
     } else {
