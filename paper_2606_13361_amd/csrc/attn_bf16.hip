@@ -1,6 +1,7 @@
 // attn_bf16.hip -- causal grouped-query attention with a query offset, bf16
 // in, fp32 accumulate, for gfx950 (MI355X): the register-staged member of the
-// kernel family.  It serves every mode at head_dim 64 and continuations of
+// kernel family.  It serves every mode at head_dim 64 (short prefills run on
+// attn_pk.hip) and continuations of
 // more than 96 query rows per kv head at head_dim 128 that are not yet long
 // enough for the two-group kernel (attn_pp.hip), which runs prefill and many
 // readers at head_dim 128; shorter continuations run on attn_rows.hip /
@@ -212,8 +213,8 @@ void attn_bf16_kernel(const AttnParams p) {
 template <int D, class E>
 hipError_t launch_d(const AttnParams &p, int mode, int grid, hipStream_t s) {
     switch (mode) {
-        case kModePrefill:
-            hipLaunchKernelGGL((attn_bf16_kernel<D, kModePrefill, E>), dim3(grid), dim3(THREADS), 0, s, p);
+        case kModePrefill:   // D = 64 only
+            hipLaunchKernelGGL((attn_bf16_kernel<64, kModePrefill, E>), dim3(grid), dim3(THREADS), 0, s, p);
             break;
         case kModeContinue:
             hipLaunchKernelGGL((attn_bf16_kernel<D, kModeContinue, E>), dim3(grid), dim3(THREADS), 0, s, p);
@@ -228,6 +229,7 @@ hipError_t launch_d(const AttnParams &p, int mode, int grid, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_attn_bf16(const AttnParams &p, int head_dim, int mode, bool f16, int grid, hipStream_t s) {
+    if (mode == kModePrefill && p.split_keys) return launch_attn_pk(p, head_dim, f16, grid, s);
     if (f16) return head_dim == 128 ? launch_d<128, F16>(p, mode, grid, s) : launch_d<64, F16>(p, mode, grid, s);
     return head_dim == 128 ? launch_d<128, Bf16>(p, mode, grid, s) : launch_d<64, Bf16>(p, mode, grid, s);
 }

@@ -86,6 +86,30 @@ int rows_per_tile(const kvr_desc *d, int64_t rows) {
     return rows / kRowsF32 * d->n_kv_heads >= kF32WideTiles ? kRowsF32 : kRowsF32 / 2;
 }
 
+// A 16-bit prefill takes at least its longest row tile, the one that sees every
+// key.  The key-split kernel (attn_pk.hip: tiles of 128 rows whose keys two
+// groups of waves share) halves that.
+//   head_dim 128, against 256-row tiles that every wave runs whole: pays while the
+//   256-row tiles leave compute units idle.  From 3/4 of them on, the second
+//   128-row workgroup of a compute unit costs its fixed time (query rows, first
+//   tiles, epilogue), about what 24 key tiles save.  Measured 256 -> 128 rows, 32 / 8
+//   heads: 255 tokens 14.9 -> 12.3 us, 945 30.8 -> 23.3, 1300 38.4 -> 28.5, 1900 (240
+//   workgroups of 256 rows, 30 key tiles) 51.5 -> 46.2; 64 / 8 heads, 900 (232, 15
+//   key tiles) 35.6 -> 36.8; beyond: 2800 (352) 78.7 -> 89.3.
+//   head_dim 64, against the register-staged 128-row tiles (two workgroups per
+//   compute unit): pays in one round of workgroups, and in two where the longest
+//   tile is long.  16 / 2 heads, 2047 tokens 42.8 -> 29.3 us, 4000 (500 workgroups)
+//   82.7 -> 58.9, 32 / 8 heads 2000 (504) 44.7 -> 38.4; 64 / 8 heads 1000 (500, 16 key
+//   tiles) 25.1 -> 26.1; beyond: 16 / 2 heads 8000 (1000) 179 -> 191.
+constexpr int64_t kPkLongTokens = 23 * kKeyTile;
+bool use_pk(const kvr_desc *d, int64_t rows, int64_t n_tok) {
+    const int64_t tile = d->head_dim == 64 ? kRowsPK : kRowsPP;
+    const int64_t wgs = (rows + tile - 1) / tile * d->n_kv_heads;
+    const int64_t any = d->head_dim == 64 ? kCus : kCus * 3 / 4 - 1;
+    const int64_t most = d->head_dim == 64 ? 2 * kCus : kCus - 1;
+    return wgs <= any || (wgs <= most && n_tok > kPkLongTokens);
+}
+
 struct Split {
     int32_t nsplit;
     int64_t chunk;
@@ -377,7 +401,9 @@ int launch_single(const kvr_desc *d, int mode, const void *Q, const void *K, con
         else
             e = launch_attn_rows(p, f16(d), (int)grid, stream);
     } else if (mode == kModePrefill && use_pp(d)) {
-        const int64_t pp_tiles = (rows + kRowsPP - 1) / kRowsPP;
+        p.split_keys = use_pk(d, rows, n_tok);
+        const int64_t rows_wg = p.split_keys ? kRowsPK : kRowsPP;
+        const int64_t pp_tiles = (rows + rows_wg - 1) / rows_wg;
         p.tiles_total = (int32_t)pp_tiles;
         e = launch_attn_pp(p, kModePrefill, f16(d), (int)(pp_tiles * p.n_kv_heads), stream);
     } else if (mode == kModeContinue && use_pp_long(d, n_prefix, n_tok, sp)) {
@@ -389,6 +415,7 @@ int launch_single(const kvr_desc *d, int mode, const void *Q, const void *K, con
         e = launch_attn_pp(p, kModeContinue, f16(d),
                            (int)((lp.tail0 + (lp.tiles - lp.tail0) * lp.nsplit) * p.n_kv_heads), stream);
     } else if (is16(d)) {
+        p.split_keys = mode == kModePrefill && use_pk(d, rows, n_tok);
         e = launch_attn_bf16(p, d->head_dim, mode, f16(d), (int)grid, stream);
     } else {
         if (mode == kModePrefill && !keys_in_cache) {   // the fp32 kernel does not write the cache itself

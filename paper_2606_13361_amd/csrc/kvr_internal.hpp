@@ -54,6 +54,7 @@ struct AttnParams {
     // nsplit key splits each (tiles_total: none)
     int32_t tail_tile0;
     int32_t row_tile;    // fp32 path: query rows per workgroup, 16 or 32
+    int32_t split_keys;  // 16-bit prefill: 1 runs the key-split kernel (row tiles of kRowsPK)
     int32_t seg_tok0[kMaxSegments + 1];   // packed token offset of each segment (cu_seqlens)
     int32_t seg_tile0[kMaxSegments + 1];  // first row tile of each segment (prefix sums; not used
                                           // by the two-group kernel, whose reader tiles are packed)
@@ -96,6 +97,10 @@ hipError_t launch_merge_bf16(const MergeParams &p, int head_dim, bool f16, hipSt
 // matrix and softmax steps
 constexpr int kRowsPP = 256;   // query rows per workgroup (8 waves x 32)
 hipError_t launch_attn_pp(const AttnParams &p, int mode, bool f16, int grid, hipStream_t s);
+// 16-bit prefill with the keys split between the two groups (D in {64, 128});
+// launch_attn_pp (D = 128) and launch_attn_bf16 (D = 64) run it for split_keys
+constexpr int kRowsPK = 128;   // query rows per workgroup
+hipError_t launch_attn_pk(const AttnParams &p, int head_dim, bool f16, int grid, hipStream_t s);
 // bf16 continuation for G*S <= 96 rows (D = 128).  33..96 rows: the waves of
 // a workgroup split the rows and share one ring of key stages; up to 32 rows
 // (decode steps) and the int8 artifact: the waves split the keys
