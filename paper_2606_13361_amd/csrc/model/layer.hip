@@ -12,6 +12,8 @@
 
 #include "attn_common.hpp"
 #include "kvr_model.h"
+#include "silu.hpp"
+#include "skinny.hpp"
 
 namespace kvr {
 namespace model {
@@ -126,15 +128,6 @@ __global__ __launch_bounds__(NT) void qk_norm_rope_kernel(const QkParams p) {
         put(p.k + (t * p.Hkv + g) * D, y1, y2);
         if (p.kc) put(p.kc + ((int64_t)g * p.cap + pos) * D, y1, y2);
     }
-}
-
-// silu(g) = g / (1 + e^-g) with the hardware exponential (2^x) and reciprocal
-// (each within about an ulp of fp32): the product with the up row is rounded to
-// the element format, far coarser.  Large -g gives 2^x = inf, rcp = 0, silu = -0.
-// One definition for the multi-row kernel and the one-row prologue, so a
-// continuation step and a prefill give the same activation bits.
-__device__ __forceinline__ float silu(float g) {
-    return g * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(g * -1.4426950408889634f));
 }
 
 // act[t][i] = silu(gu[t][i]) * gu[t][I + i], 8 elements per thread.
@@ -675,9 +668,36 @@ int kvr_layer_forward(const kvr_desc *desc, const kvr_layer_shape *shape, const 
     // hipBLASLt products
     const bool one = T == 1 && H <= kGemvMaxK && I <= kGemvMaxK && Hq * D <= kGemvMaxK;
 
+    // a few tokens: this library's products (skinny.hpp); the packed rows, the
+    // activation and the partial sums go where the library products' workspace
+    // would
+    const size_t pk_b = up256(packed_bytes(T, H)), act_b = up256((size_t)T * I * 2);
+    const bool few = skinny_ok(T, H, I, Hq * D) && pk_b + act_b + part_bytes(T, H) <= KVR_BLAS_WORKSPACE_BYTES;
+    uint16_t *const hb = (uint16_t *)h, *const xp = (uint16_t *)(b + lw.blas);
+    uint16_t *const act = (uint16_t *)(b + lw.blas + pk_b);
+    float *const part = (float *)(b + lw.blas + pk_b + act_b);
+    const bool half = dt == KVR_F16;
+    auto ok = [](hipError_t e) { return e == hipSuccess; };
+    auto product = [&](const void *x, const void *wt, int K, int64_t N, void *y) {
+        SkinnyParams p;
+        p.x = (const uint16_t *)x;
+        p.w = (const uint16_t *)wt;
+        p.y = (uint16_t *)y;
+        p.part = part;
+        p.N = N;
+        p.K = K;
+        p.T = (int32_t)T;
+        p.rows = 0;
+        return p;
+    };
+
     // attention block
     if (one) {
         if ((st = gemv(dt, kNorm, h, w->ln1, shape->eps, w->wqkv, H, Wq, 0, b + lw.qkv, s))) return st;
+    } else if (few) {
+        if (!ok(launch_residual(hb, nullptr, (const uint16_t *)w->ln1, xp, (int)T, H, shape->eps, half, s)) ||
+            !ok(launch_skinny_norm(product(xp, w->wqkv, H, Wq, b + lw.qkv), false, half, s)))
+            return KVR_ERR_DEVICE;
     } else {
         if ((st = kvr_rmsnorm(dt, h, w->ln1, T, H, shape->eps, b + lw.xn, stream))) return st;
         if ((st = linear(bl, dt, b + lw.xn, w->wqkv, T, H, Wq, 0.f, b + lw.qkv, blws, KVR_BLAS_WORKSPACE_BYTES, s)))
@@ -716,6 +736,15 @@ int kvr_layer_forward(const kvr_desc *desc, const kvr_layer_shape *shape, const 
         st = kvr_continue(desc, b + lw.q, b + lw.k, b + lw.v, kcache, vcache, L_prefix, T, b + lw.att,
                           b + lw.split, lw.blas - lw.split, stream);
     if (st) return st;
+    if (few) {
+        if (!ok(launch_skinny_split(product(b + lw.att, w->wo, Hq * D, H, nullptr), half, s)) ||
+            !ok(launch_residual(hb, part, (const uint16_t *)w->ln2, xp, (int)T, H, shape->eps, half, s)) ||
+            !ok(launch_skinny_norm(product(xp, w->wgu, H, I, act), true, half, s)) ||
+            !ok(launch_skinny_split(product(act, w->wd, I, H, nullptr), half, s)) ||
+            !ok(launch_residual(hb, part, nullptr, nullptr, (int)T, H, 0.f, half, s)))
+            return KVR_ERR_DEVICE;
+        return KVR_OK;
+    }
     if ((st = linear(bl, dt, b + lw.att, w->wo, T, Hq * D, H, 1.f, h, blws, KVR_BLAS_WORKSPACE_BYTES, s)))
         return st;
     // MLP block
