@@ -335,7 +335,8 @@ int kvr_prefill_rope(const kvr_desc *desc, const kvr_rope *rope, const void *Q, 
  * kvr_rope_apply + kvr_cache_append).  append != 0 also writes the rotated Ks
  * and the Vs into cache rows [L_prefix, L_prefix + S) (a decode step in one
  * call; needs L_prefix + S <= capacity); append == 0 leaves the cache
- * untouched.  The rotated Qs/Ks rows go through ws:
+ * untouched.  The rotated Qs/Ks rows go through ws (16-bit continuations of up
+ * to 8 tokens at head_dim 128 may rotate them inside the attention kernel instead):
  * ws_bytes >= kvr_workspace_bytes_rope(desc, L_prefix, S, 1).
  * Needs rope->n_pos >= L_prefix + S.
  */

@@ -13,6 +13,13 @@
 // MFMA accumulation chains).  The query rows reach LDS by the same direct
 // loads, issued together with each wave's first K/V stage.
 //
+// Up to kFusedTokens tokens may arrive unrotated (and, from a decoder layer,
+// unnormalized): the query rows and the new key rows are then rotated in LDS after
+// they land, and the rotated keys go to the cache from there, which saves the
+// pre-pass launch (with the cache update, host-issued: one token over 3774 rows
+// 17.3 -> 14.1 us, over 32001 31.2 -> 27.7; in a 12-layer one-token step the norm and
+// rotation launch as well, 887 -> 862 us).
+//
 // Merge with a single barrier: every wave posts its (m, l) and the three
 // head-dim quarters of O it does not own; wave w then owns quarter w, sums the
 // four contributions scaled to the common maximum in a fixed order, and
@@ -42,6 +49,11 @@ constexpr int RING = NSW * STAGE;            // 32 KB per wave
 constexpr int RINGS = 4 * RING;              // 128 KB
 constexpr int QROWS = 96;                    // query rows held in LDS
 constexpr int LDS_BYTES = RINGS + QROWS * ROWB;   // + 24 KB of Q
+// rotation in the kernel: the tokens' table rows (512 bytes each), then the norm
+// weights of queries and keys
+constexpr int CSB = D * 4;
+constexpr int FUSE_BYTES = kFusedTokens * CSB + 4 * ROWB;   // (a direct load writes 1 KB)
+static_assert(kFusedTokens % 2 == 0 && LDS_BYTES + FUSE_BYTES <= 160 * 1024, "fused rows exceed the LDS");
 
 // merge buffers, reusing the rings and Q: O quarters [4 owners][3 sources][NCT][4][64 lanes]
 // as float4, then m and l [4 waves][NCT][64 lanes]
@@ -51,6 +63,83 @@ static_assert(merge_bytes<3>() <= LDS_BYTES, "merge buffers exceed the LDS alloc
 
 __device__ __forceinline__ int swz(int row) { return ((row >> 2) & 3) | ((row & 3) << 2); }
 
+
+// Rotation in the kernel, in LDS: eight lanes a row, lane c of them dims 8c ..
+// 8c + 7 and their partners 64 further (the norm's sum of squares meets in the
+// eight), the same operations and rounding as the pre-pass.  fuse_lds: the tokens'
+// table rows; nw: the row's norm weights (read only with p.q_norm).
+template <class E>
+__device__ __forceinline__ void rotate_row(const AttnParams &p, unsigned char *rows, int row, int c, int tk,
+                                           const unsigned char *fuse_lds, const unsigned char *nw, u32x4 &lo, u32x4 &hi) {
+    u32x4 *pl = (u32x4 *)(rows + row * ROWB + 16 * (c ^ swz(row)));
+    u32x4 *ph = (u32x4 *)(rows + row * ROWB + 16 * ((c + 8) ^ swz(row)));
+    lo = *pl;
+    hi = *ph;
+    const float *cs = (const float *)(fuse_lds + tk * CSB) + 16 * c;
+    if (p.q_norm) {
+        float ss = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            ss = __builtin_fmaf(E::lo(lo[w]), E::lo(lo[w]), ss);
+            ss = __builtin_fmaf(E::hi(lo[w]), E::hi(lo[w]), ss);
+            ss = __builtin_fmaf(E::lo(hi[w]), E::lo(hi[w]), ss);
+            ss = __builtin_fmaf(E::hi(hi[w]), E::hi(hi[w]), ss);
+        }
+        ss += __shfl_xor(ss, 1);
+        ss += __shfl_xor(ss, 2);
+        ss += __shfl_xor(ss, 4);
+        const float inv = 1.0f / sqrtf(ss / (float)D + p.norm_eps);
+        const u32x4 wl = *(const u32x4 *)(nw + 16 * c), wh = *(const u32x4 *)(nw + 16 * (c + 8));
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            float a1, a2, b1, b2;
+            rope_rot(E::lo(lo[w]) * inv * E::lo(wl[w]), E::lo(hi[w]) * inv * E::lo(wh[w]), cs[4 * w], cs[4 * w + 1],
+                     a1, a2);
+            rope_rot(E::hi(lo[w]) * inv * E::hi(wl[w]), E::hi(hi[w]) * inv * E::hi(wh[w]), cs[4 * w + 2],
+                     cs[4 * w + 3], b1, b2);
+            lo[w] = E::pack2(a1, b1);
+            hi[w] = E::pack2(a2, b2);
+        }
+    } else {
+        rope_rot8<E>(lo, hi, cs);
+    }
+    *pl = lo;
+    *ph = hi;
+}
+
+// Row item / 8 of a stage, if it is a new key (keys [npre, ke)): rotated, and with
+// p.kc_app on to the cache from here, with its values.
+template <class E>
+__device__ __forceinline__ void rotate_new(const AttnParams &p, const unsigned char *fuse_lds, unsigned char *st, int g,
+                                           int64_t key0, int64_t ke, int item) {
+    const int row = item >> 3, c = item & 7;
+    const int64_t key = key0 + row;
+    if (key < p.n_prefix || key >= ke) return;
+    u32x4 lo, hi;
+    rotate_row<E>(p, st, row, c, (int)(key - p.n_prefix), fuse_lds, fuse_lds + kFusedTokens * CSB + ROWB, lo, hi);
+    if (p.kc_app) {
+        unsigned char *kd = (unsigned char *)p.kc_app + ((int64_t)g * p.cap + key) * ROWB;
+        unsigned char *vd = (unsigned char *)p.vc_app + ((int64_t)g * p.cap + key) * ROWB;
+        *(u32x4 *)(kd + 16 * c) = lo;
+        *(u32x4 *)(kd + 16 * (c + 8)) = hi;
+        const unsigned char *vr = st + HALF + row * ROWB;
+        *(u32x4 *)(vd + 16 * c) = *(const u32x4 *)(vr + 16 * (c ^ swz(row)));
+        *(u32x4 *)(vd + 16 * (c + 8)) = *(const u32x4 *)(vr + 16 * ((c + 8) ^ swz(row)));
+    }
+}
+
+// The new keys of a wave's own stage.  (Takes its place from the block and thread
+// index: nothing more for the stage loop's closure to hold, which moves the other
+// instances' register allocation.)
+template <class E>
+__device__ __forceinline__ void rotate_stage(const AttnParams &p, const unsigned char *fuse_lds, unsigned char *st,
+                                             int64_t key0) {
+    const int g = blockIdx.x % p.n_kv_heads;
+    if (key0 + SKEYS <= p.n_prefix || (int)(blockIdx.x / p.n_kv_heads) != p.nsplit - 1) return;
+    for (int i = threadIdx.x & 63; i < 8 * SKEYS; i += 64)
+        rotate_new<E>(p, fuse_lds, st, g, key0, p.n_prefix + p.seg_tok0[1], i);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
 
 // Head-dim quarter MT of every column tile: the four waves' contributions,
 // each scaled by 2^(m_w - M) with M the largest m_w, summed in wave order
@@ -158,10 +247,12 @@ __device__ __forceinline__ void codes_to_bf16(const u32x4 w, u32x4 &lo, u32x4 &h
 // are scaled by s_K inside the softmax exponent, the cached part of O by s_V
 // before the first new key (or at the end); the new rows stay bf16.  Cached
 // and new keys then never share a stage.
-template <int NCT, bool Q8, class E>
+// FUSE: q and the new keys arrive unrotated (see above).
+template <int NCT, bool Q8, class E, bool FUSE = false>
 __global__ __launch_bounds__(THREADS) void attn_cont_kernel(const AttnParams p) {
+    static_assert(!(Q8 && FUSE), "the int8 artifact's callers rotate their rows");
     static_assert(!Q8 || std::is_same<E, Bf16>::value, "the int8 artifact is a bf16 model's");
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[LDS_BYTES];
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[LDS_BYTES + (FUSE ? FUSE_BYTES : 0)];
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: scalar branches
@@ -202,11 +293,12 @@ __global__ __launch_bounds__(THREADS) void attn_cont_kernel(const AttnParams p) 
     const int my_n = nmain > wave ? (nmain - wave + 3) / 4 : 0;
     auto is_q8 = [&](int t) { return Q8 && wave + 4 * t < n_cst; };
 
-    const int64_t nstride_b = (int64_t)p.n_kv_heads * ROWB;
+    const int64_t nstride_b = FUSE ? p.new_tok_stride * 2 : (int64_t)p.n_kv_heads * ROWB;
+    const int64_t nhead_b = FUSE ? p.new_head_stride * 2 : ROWB;
     const unsigned char *kc0 = (const unsigned char *)p.kc + (int64_t)g * p.cap * ROWB;
     const unsigned char *vc0 = (const unsigned char *)p.vc + (int64_t)g * p.cap * ROWB;
-    const unsigned char *kn0 = (const unsigned char *)p.kn + (int64_t)g * ROWB;
-    const unsigned char *vn0 = (const unsigned char *)p.vn + (int64_t)g * ROWB;
+    const unsigned char *kn0 = (const unsigned char *)p.kn + g * nhead_b;
+    const unsigned char *vn0 = (const unsigned char *)p.vn + g * nhead_b;
     uint32_t lchunk[8], off_c[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -300,9 +392,25 @@ __global__ __launch_bounds__(THREADS) void attn_cont_kernel(const AttnParams p) 
     // row R-1: their columns are computed and never stored), then this wave's
     // first stage; Q is older than the stage in the wave's load queue
     const unsigned char *qlds = smem + RINGS;
+    if constexpr (FUSE) {
+        // the tokens' table rows and the norm weights, older than everything else in
+        // wave 0's queue
+        unsigned char *cslds = smem + LDS_BYTES;
+        if (wave == 0) {
+            for (int i = 0; 2 * i < S; ++i) {
+                const int t = min(2 * i + (lane >> 5), S - 1);
+                dma16((const void *)(p.rope + (npre + t) * D + 4 * (lane & 31)), cslds + 2 * i * CSB);
+            }
+            // 16 lanes each; lanes 32 .. 63 write the same again behind them
+            if (p.q_norm) {
+                const uint64_t a = (uint64_t)(uintptr_t)((lane & 16) ? p.k_norm : p.q_norm) + 16u * (lane & 15);
+                dma16((const void *)a, cslds + kFusedTokens * CSB);
+            }
+        }
+    }
     {
         const uint64_t q_a = (uint64_t)(uintptr_t)p.q + (uint64_t)g * G * ROWB;
-        const uint64_t qtok_b = (uint64_t)p.n_q_heads * ROWB;
+        const uint64_t qtok_b = FUSE ? (uint64_t)p.q_tok_stride * 2 : (uint64_t)p.n_q_heads * ROWB;
 #pragma unroll
         for (int i = 0; i < 2 * NCT; ++i) {
             const int base = 4 * (2 * NCT * wave + i);
@@ -340,6 +448,20 @@ __global__ __launch_bounds__(THREADS) void attn_cont_kernel(const AttnParams p) 
     }
     __builtin_amdgcn_s_barrier();       // all of Q (and the split suffix stage) is in LDS
     asm volatile("" ::: "memory");
+
+    if constexpr (FUSE) {
+        const unsigned char *fuse_lds = smem + LDS_BYTES;
+        u32x4 lo, hi;
+        for (int i = tid; i < 8 * R; i += THREADS)
+            rotate_row<E>(p, smem + RINGS, i >> 3, i & 7, div_small(i >> 3, inv_g), fuse_lds, fuse_lds + kFusedTokens * CSB,
+                          lo, hi);
+        if (sfx_split)
+            for (int i = tid; i < 8 * SKEYS; i += THREADS)
+                rotate_new<E>(p, fuse_lds, smem + 3 * RING + STAGE, g, kb + (int64_t)SKEYS * (nst - 1), ke, i);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    }
 
     bool o_scaled = !Q8;                // Q8: cached part of O still in code units of V
     auto scale_o = [&]() {
@@ -494,6 +616,7 @@ __global__ __launch_bounds__(THREADS) void attn_cont_kernel(const AttnParams p) 
                                 : kb + (int64_t)i_st * SKEYS;
         const unsigned char *ks_ = smem + ring_lds + (t % NSW) * STAGE;
         const unsigned char *vs_ = ks_ + HALF;
+        if constexpr (FUSE) rotate_stage<E>(p, smem + LDS_BYTES, smem + ring_lds + (t % NSW) * STAGE, key0);
         if constexpr (Q8 && !q8) {
             if (!o_scaled) scale_o();
         }
@@ -552,22 +675,24 @@ __global__ __launch_bounds__(THREADS) void attn_cont_kernel(const AttnParams p) 
         case 2: finish_quarter<E, NCT, 2>(p, rs, obuf, lbuf, mbuf, valid, tok, head, g, split, lane); break;
         default: finish_quarter<E, NCT, 3>(p, rs, obuf, lbuf, mbuf, valid, tok, head, g, split, lane); break;
     }
-    if (!Q8 && p.kc_app && (p.nsplit == 1 || last_split)) append_new_rows<ROWB>(p, g, S, tid, THREADS);
+    if (!Q8 && !FUSE && p.kc_app && (p.nsplit == 1 || last_split)) append_new_rows<ROWB>(p, g, S, tid, THREADS);
 }
 
 }  // namespace
 
-template <bool Q8, class E>
+template <bool Q8, class E, bool FUSE = false>
 void launch_nct(const AttnParams &p, int ncol_tiles, int grid, hipStream_t s) {
     switch (ncol_tiles) {
-        case 1: hipLaunchKernelGGL((attn_cont_kernel<1, Q8, E>), dim3(grid), dim3(THREADS), 0, s, p); break;
-        case 2: hipLaunchKernelGGL((attn_cont_kernel<2, Q8, E>), dim3(grid), dim3(THREADS), 0, s, p); break;
-        default: hipLaunchKernelGGL((attn_cont_kernel<3, Q8, E>), dim3(grid), dim3(THREADS), 0, s, p); break;
+        case 1: hipLaunchKernelGGL((attn_cont_kernel<1, Q8, E, FUSE>), dim3(grid), dim3(THREADS), 0, s, p); break;
+        case 2: hipLaunchKernelGGL((attn_cont_kernel<2, Q8, E, FUSE>), dim3(grid), dim3(THREADS), 0, s, p); break;
+        default: hipLaunchKernelGGL((attn_cont_kernel<3, Q8, E, FUSE>), dim3(grid), dim3(THREADS), 0, s, p); break;
     }
 }
 
 hipError_t launch_attn_cont(const AttnParams &p, int ncol_tiles, bool q8, bool f16, int grid, hipStream_t s) {
     if (q8) launch_nct<true, Bf16>(p, ncol_tiles, grid, s);
+    else if (p.rope && f16) launch_nct<false, F16, true>(p, ncol_tiles, grid, s);
+    else if (p.rope) launch_nct<false, Bf16, true>(p, ncol_tiles, grid, s);
     else if (f16) launch_nct<false, F16>(p, ncol_tiles, grid, s);
     else launch_nct<false, Bf16>(p, ncol_tiles, grid, s);
     return hipGetLastError();

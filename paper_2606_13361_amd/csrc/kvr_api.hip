@@ -273,6 +273,7 @@ void fill_common(AttnParams &p, const kvr_desc *d) {
     p.nsplit = 1;
     p.new_tok_stride = (int64_t)d->n_kv_heads * d->head_dim;
     p.new_head_stride = d->head_dim;
+    p.q_tok_stride = (int64_t)d->n_q_heads * d->head_dim;
 }
 
 // RoPE table argument of a call that rotates positions [0, n_pos_needed)
@@ -331,16 +332,34 @@ int append_impl(const kvr_desc *d, const void *Ks, const void *Vs, int64_t S, vo
     return to_status(launch_append(a, stream));
 }
 
+// Continuations on the keys-split or row-split kernel (use_cont): the row split
+// removes the in-workgroup merge and the suffix stage that one wave alone would
+// run, but spends about a third more matrix and softmax work per key (24 of 32
+// MFMA columns, every wave on every stage): it pays for short key ranges per
+// workgroup and more than 32 rows.  Decode steps (one column tile), long ranges and
+// the int8 artifact use the kernel whose waves split the keys.
+bool use_keys_split(const kvr_desc *d, int64_t n_prefix, int64_t n_tok, const Split &sp) {
+    const int64_t keys_per_wg = sp.nsplit > 1 ? sp.chunk : n_prefix + n_tok;
+    return (int64_t)(d->n_q_heads / d->n_kv_heads) * n_tok <= 32 || keys_per_wg > kRowsSplitMaxKeys;
+}
+
+// Whether the attention kernel of a continuation rotates its rows itself.
+bool fuse_rope(const kvr_desc *d, int64_t n_prefix, int64_t n_tok, const Split &sp) {
+    return use_cont(d, n_tok) && n_tok <= kFusedTokens && use_keys_split(d, n_prefix, n_tok, sp);
+}
+
 // mode kModePrefill: kc/vc are the caches to fill (bf16: in the attention
 // kernel itself); kModeContinue: kc/vc are the cached prefix (read only).
 // qscale != NULL: continuation over the int8 artifact (kc/vc are its codes).
 // rope != NULL (prefill): rotate the query rows in registers, and read the
 // already rotated keys and the values back from kc/vc instead of K/V (the
 // RoPE pre-pass wrote them there); the kernel then writes no cache rows.
+// rope != NULL (continue, fuse_rope shapes only): the kernel rotates Q and K; raw:
+// they are parts of fused q|k|v rows, normalized first.
 int launch_single(const kvr_desc *d, int mode, const void *Q, const void *K, const void *V, void *kc,
                   void *vc, int64_t n_prefix, int64_t n_tok, void *out, const Split &sp, void *ws,
                   hipStream_t stream, const float *qscale = nullptr, const float *rope = nullptr,
-                  bool append = false) {
+                  bool append = false, const QkvRows *raw = nullptr) {
     AttnParams p;
     fill_common(p, d);
     p.q = Q; p.kn = K; p.vn = V; p.out = out;
@@ -358,6 +377,14 @@ int launch_single(const kvr_desc *d, int mode, const void *Q, const void *K, con
     } else {
         p.kc = kc;
         p.vc = vc;
+        p.rope = rope;
+        if (raw) {
+            const int64_t w = (int64_t)(d->n_q_heads + 2 * d->n_kv_heads) * d->head_dim;
+            p.q_norm = raw->q_norm;
+            p.k_norm = raw->k_norm;
+            p.norm_eps = raw->eps;
+            p.q_tok_stride = p.new_tok_stride = w;
+        }
     }
     p.ws = (float *)ws;
     p.qscale = qscale;
@@ -383,20 +410,13 @@ int launch_single(const kvr_desc *d, int mode, const void *Q, const void *K, con
     if (grid > 0x7fffffff) return KVR_ERR_SHAPE;
     hipError_t e;
     if (mode == kModeContinue && use_cont(d, n_tok)) {
-        // The row split removes the in-workgroup merge and the suffix stage
-        // that one wave alone would run, but spends about a third more matrix
-        // and softmax work per key (24 of 32 MFMA columns, every wave on every
-        // stage): it pays for short key ranges per workgroup and more than 32
-        // rows.  Decode steps (one column tile), long ranges and the int8
-        // artifact use the kernel whose waves split the keys.
         const int nct = (int)((rows + 31) / 32);
-        const int64_t keys_per_wg = p.nsplit > 1 ? p.chunk : n_prefix + n_tok;
         if (append) {            // both kernels store the new rows themselves
             p.kc_app = kc;
             p.vc_app = vc;
             append = false;
         }
-        if (qscale || nct == 1 || keys_per_wg > kRowsSplitMaxKeys)
+        if (qscale || use_keys_split(d, n_prefix, n_tok, sp))
             e = launch_attn_cont(p, nct, qscale != nullptr, f16(d), (int)grid, stream);
         else
             e = launch_attn_rows(p, f16(d), (int)grid, stream);
@@ -567,6 +587,23 @@ int check_continue(const kvr_desc *desc, const void *Qs, const void *Ks, const v
 }
 
 }  // namespace
+
+bool fused_rows_ok(const kvr_desc *d, int64_t L_prefix, int64_t S) {
+    return fuse_rope(d, L_prefix, S, plan_split(d, L_prefix, S));
+}
+
+int continue_fused_rows(const kvr_desc *d, const QkvRows &rows, const float *cos_sin, void *kcache, void *vcache,
+                        int64_t L_prefix, int64_t S, void *out, void *ws, size_t ws_bytes, hipStream_t stream) {
+    const int st = check_desc(d);
+    if (st) return st;
+    const Split sp = plan_split(d, L_prefix, S);
+    if (ws_bytes < sp.ws_bytes) return KVR_ERR_WORKSPACE;
+    const unsigned char *q = (const unsigned char *)rows.qkv;
+    const size_t head_b = (size_t)d->head_dim * elt_bytes(d);
+    return launch_single(d, kModeContinue, q, q + d->n_q_heads * head_b, q + (d->n_q_heads + d->n_kv_heads) * head_b,
+                         kcache, vcache, L_prefix, S, out, sp, ws, stream, nullptr, cos_sin, true, &rows);
+}
+
 }  // namespace kvr
 
 // The split partials of kvr_continue_noalloc: a fixed buffer, one copy per
@@ -861,6 +898,10 @@ int kvr_continue_rope(const kvr_desc *desc, const kvr_rope *rope, const void *Qs
         !aligned16(vcache) || !aligned16(ws))
         return KVR_ERR_ALIGN;
     unsigned char *wsb = (unsigned char *)ws;
+    const Split sp = plan_split(desc, L_prefix, S);
+    if (fuse_rope(desc, L_prefix, S, sp))
+        return launch_single(desc, kModeContinue, Qs, Ks, Vs, kcache, vcache, L_prefix, S, out, sp, ws,
+                             (hipStream_t)stream, nullptr, rope->cos_sin, append != 0);
     // the rows at positions L_prefix..: queries and keys rotated into the
     // workspace, and with append the rotated keys and the values into the cache
     RopeParams rp = rope_params(desc, rope, S, L_prefix);
@@ -877,7 +918,6 @@ int kvr_continue_rope(const kvr_desc *desc, const kvr_rope *rope, const void *Qs
         rp.job[1].vcache = vcache;
     }
     if (launch_rope(rp, desc->head_dim, desc->dtype, (hipStream_t)stream) != hipSuccess) return KVR_ERR_DEVICE;
-    const Split sp = plan_split(desc, L_prefix, S);
     return launch_single(desc, kModeContinue, wsb + w.q_off, wsb + w.k_off, Vs, kcache, vcache, L_prefix, S, out,
                          sp, ws, (hipStream_t)stream);
 }

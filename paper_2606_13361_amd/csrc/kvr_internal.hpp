@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "kvr.h"
+
 namespace kvr {
 
 // Readers handled by one launch of the attention kernel; kvr_continue_batched
@@ -26,13 +28,15 @@ struct AttnParams {
     float *ws;       // split partials: O [nsplit][Hkv][rows][D], then (m, l) [nsplit][Hkv][rows][2]
     const float *qscale;   // int8 artifact continuation: {s_K, s_V} (kc/vc then point at the codes)
     // RoPE table [pos][D/2] of (cos, sin), or null.  Set for prefill and many
-    // readers only: those kernels rotate each query row in registers at its
-    // position n_prefix + token (continuations get their rows rotated by the
-    // pre-pass instead).
+    // readers (those kernels rotate each query row in registers at its position
+    // n_prefix + token) and for continuations of at most kFusedTokens tokens on the
+    // keys-split kernel, which rotates their query and new key rows in LDS; other
+    // continuations get their rows rotated by the pre-pass instead.
     const float *rope;
     // Element strides of kn/vn: token and kv head.  Token-major new rows have
     // (n_kv_heads * D, D); prefill with RoPE reads its rotated rows back from
-    // the cache, (D, cap * D).  Honoured by the prefill / readers kernels.
+    // the cache, (D, cap * D).  Honoured by the prefill / readers kernels and the
+    // keys-split kernel.
     int64_t new_tok_stride, new_head_stride;
     // Continuation with the cache update: the workgroup that reads the new
     // rows of a kv head last (the last split) also stores them into rows
@@ -53,11 +57,16 @@ struct AttnParams {
     // many readers on the two-group kernel: row tiles from this one on run as
     // nsplit key splits each (tiles_total: none)
     int32_t tail_tile0;
-    int32_t row_tile;    // fp32 path: query rows per workgroup, 16 or 32
-    int32_t split_keys;  // 16-bit prefill: 1 runs the key-split kernel (row tiles of kRowsPK)
     int32_t seg_tok0[kMaxSegments + 1];   // packed token offset of each segment (cu_seqlens)
     int32_t seg_tile0[kMaxSegments + 1];  // first row tile of each segment (prefix sums; not used
                                           // by the two-group kernel, whose reader tiles are packed)
+    // With rope on the keys-split kernel: RMSNorm weights [D] applied to the query
+    // and new key rows before the rotation (a decoder layer's q/k norm), or null.
+    const void *q_norm, *k_norm;
+    float norm_eps;
+    int64_t q_tok_stride;  // elements between tokens of q (keys-split kernel, with rope)
+    int32_t row_tile;    // fp32 path: query rows per workgroup, 16 or 32
+    int32_t split_keys;  // 16-bit prefill: 1 runs the key-split kernel (row tiles of kRowsPK)
 };
 
 struct AppendParams {
@@ -105,6 +114,7 @@ hipError_t launch_attn_pk(const AttnParams &p, int head_dim, bool f16, int grid,
 // a workgroup split the rows and share one ring of key stages; up to 32 rows
 // (decode steps) and the int8 artifact: the waves split the keys
 constexpr int kContMaxRows = 96;
+constexpr int kFusedTokens = 8;   // the keys-split kernel rotates the rows of at most this many tokens itself
 hipError_t launch_attn_rows(const AttnParams &p, bool f16, int grid, hipStream_t s);
 hipError_t launch_attn_cont(const AttnParams &p, int ncol_tiles, bool q8, bool f16, int grid, hipStream_t s);
 // int8 artifact
@@ -137,6 +147,19 @@ struct RopeParams {
 // elt: 0 bf16, 1 fp32, 2 fp16 (kvr_dtype)
 hipError_t launch_rope(const RopeParams &p, int head_dim, int elt, hipStream_t s);
 hipError_t launch_rope_table(float *cs, int head_dim, double base, int64_t n_pos, hipStream_t s);
+
+// The attention of a decoder layer's few tokens straight from their fused q|k|v
+// rows qkv [S][(Hq + 2 Hkv) D]: per-head RMSNorm with q_norm / k_norm, rotation at
+// L_prefix + t, attention over cache rows [0, L_prefix) and the tokens themselves,
+// their rotated keys and values into cache rows [L_prefix, L_prefix + S).  For
+// shapes that fused_rows_ok names; arguments checked by the caller.
+struct QkvRows {
+    const void *qkv, *q_norm, *k_norm;
+    float eps;
+};
+bool fused_rows_ok(const kvr_desc *d, int64_t L_prefix, int64_t S);
+int continue_fused_rows(const kvr_desc *d, const QkvRows &rows, const float *cos_sin, void *kcache, void *vcache,
+                        int64_t L_prefix, int64_t S, void *out, void *ws, size_t ws_bytes, hipStream_t stream);
 
 // row-tile geometry of the two paths
 constexpr int kRowsBf16 = 128;  // query rows per workgroup, bf16 path

@@ -703,38 +703,47 @@ int kvr_layer_forward(const kvr_desc *desc, const kvr_layer_shape *shape, const 
         if ((st = linear(bl, dt, b + lw.xn, w->wqkv, T, H, Wq, 0.f, b + lw.qkv, blws, KVR_BLAS_WORKSPACE_BYTES, s)))
             return st;
     }
-    QkParams qp;
-    qp.qkv = (const uint16_t *)(b + lw.qkv);
-    qp.qn = (const uint16_t *)w->q_norm;
-    qp.kn = (const uint16_t *)w->k_norm;
-    qp.cs = rope->cos_sin;
-    qp.q = (uint16_t *)(b + lw.q);
-    qp.k = (uint16_t *)(b + lw.k);
-    qp.v = (uint16_t *)(b + lw.v);
-    // a prefill writes its own cache rows inside the attention kernel
-    qp.kc = L_prefix > 0 ? (uint16_t *)kcache : nullptr;
-    qp.vc = L_prefix > 0 ? (uint16_t *)vcache : nullptr;
-    qp.T = T;
-    qp.pos0 = L_prefix;
-    qp.cap = desc->capacity;
-    qp.Hq = Hq;
-    qp.Hkv = Hkv;
-    qp.eps = shape->eps;
-    const int64_t waves = T * (Hq + 2 * Hkv);
-    const dim3 qg((unsigned)((waves + NT / 64 - 1) / (NT / 64)));
-    if (dt == KVR_F16) {
-        if (D == 128) hipLaunchKernelGGL((qk_norm_rope_kernel<F16, 128>), qg, dim3(NT), 0, s, qp);
-        else hipLaunchKernelGGL((qk_norm_rope_kernel<F16, 64>), qg, dim3(NT), 0, s, qp);
+    if (L_prefix > 0 && kvr::fused_rows_ok(desc, L_prefix, T)) {
+        // a token or a few: the attention kernel normalizes and rotates its rows
+        // itself, and its last split writes the cache rows (one launch fewer: the norm
+        // and rotation of one token, 5 KB of work, took 4.6 us between its neighbours)
+        const kvr::QkvRows rows = {b + lw.qkv, w->q_norm, w->k_norm, shape->eps};
+        st = kvr::continue_fused_rows(desc, rows, rope->cos_sin, kcache, vcache, L_prefix, T, b + lw.att, b + lw.split,
+                                 lw.blas - lw.split, s);
     } else {
-        if (D == 128) hipLaunchKernelGGL((qk_norm_rope_kernel<Bf16, 128>), qg, dim3(NT), 0, s, qp);
-        else hipLaunchKernelGGL((qk_norm_rope_kernel<Bf16, 64>), qg, dim3(NT), 0, s, qp);
+        QkParams qp;
+        qp.qkv = (const uint16_t *)(b + lw.qkv);
+        qp.qn = (const uint16_t *)w->q_norm;
+        qp.kn = (const uint16_t *)w->k_norm;
+        qp.cs = rope->cos_sin;
+        qp.q = (uint16_t *)(b + lw.q);
+        qp.k = (uint16_t *)(b + lw.k);
+        qp.v = (uint16_t *)(b + lw.v);
+        // a prefill writes its own cache rows inside the attention kernel
+        qp.kc = L_prefix > 0 ? (uint16_t *)kcache : nullptr;
+        qp.vc = L_prefix > 0 ? (uint16_t *)vcache : nullptr;
+        qp.T = T;
+        qp.pos0 = L_prefix;
+        qp.cap = desc->capacity;
+        qp.Hq = Hq;
+        qp.Hkv = Hkv;
+        qp.eps = shape->eps;
+        const int64_t waves = T * (Hq + 2 * Hkv);
+        const dim3 qg((unsigned)((waves + NT / 64 - 1) / (NT / 64)));
+        if (dt == KVR_F16) {
+            if (D == 128) hipLaunchKernelGGL((qk_norm_rope_kernel<F16, 128>), qg, dim3(NT), 0, s, qp);
+            else hipLaunchKernelGGL((qk_norm_rope_kernel<F16, 64>), qg, dim3(NT), 0, s, qp);
+        } else {
+            if (D == 128) hipLaunchKernelGGL((qk_norm_rope_kernel<Bf16, 128>), qg, dim3(NT), 0, s, qp);
+            else hipLaunchKernelGGL((qk_norm_rope_kernel<Bf16, 64>), qg, dim3(NT), 0, s, qp);
+        }
+        if (hipGetLastError() != hipSuccess) return KVR_ERR_DEVICE;
+        if (L_prefix == 0)
+            st = kvr_prefill(desc, b + lw.q, b + lw.k, b + lw.v, T, b + lw.att, kcache, vcache, stream);
+        else
+            st = kvr_continue(desc, b + lw.q, b + lw.k, b + lw.v, kcache, vcache, L_prefix, T, b + lw.att,
+                              b + lw.split, lw.blas - lw.split, stream);
     }
-    if (hipGetLastError() != hipSuccess) return KVR_ERR_DEVICE;
-    if (L_prefix == 0)
-        st = kvr_prefill(desc, b + lw.q, b + lw.k, b + lw.v, T, b + lw.att, kcache, vcache, stream);
-    else
-        st = kvr_continue(desc, b + lw.q, b + lw.k, b + lw.v, kcache, vcache, L_prefix, T, b + lw.att,
-                          b + lw.split, lw.blas - lw.split, stream);
     if (st) return st;
     if (few) {
         if (!ok(launch_skinny_split(product(b + lw.att, w->wo, Hq * D, H, nullptr), half, s)) ||

@@ -12,7 +12,8 @@
 // every key row is read by many workgroups (all query tiles of its kv head):
 // rotating it once costs one pass over K, rotating it on every read would
 // cost one per workgroup.  Query rows of prefill and many readers are rotated
-// in registers by the attention kernels themselves (each row is read once).
+// in registers by the attention kernels themselves (each row is read once), and
+// continuations of a few tokens on the keys-split kernel rotate all their rows there.
 #include "attn_common.hpp"
 
 namespace kvr {
