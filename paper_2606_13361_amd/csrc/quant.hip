@@ -29,25 +29,44 @@ __global__ void q8_clear_kernel(float *scales) {
     if (threadIdx.x < 2) scales[threadIdx.x] = 0.f;
 }
 
-// blockIdx.y: 0 = K, 1 = V.  Each thread scans 16-byte chunks (8 values) of rows [0, L).
-__global__ __launch_bounds__(256) void q8_absmax_kernel(const QuantParams p) {
-    const uint16_t *src = (const uint16_t *)(blockIdx.y == 0 ? p.kc : p.vc);
-    const int64_t chunks = (int64_t)p.n_kv_heads * p.L * (D / 8);
+// blockIdx.y: kv head, blockIdx.z: 0 = K, 1 = V.  A head's rows [0, L) are one
+// contiguous run of 16-byte chunks, so a thread's chunks need no division; four are
+// in flight, and a workgroup issues one atomic.  Bound by HBM on large caches, by
+// the call's four launches on small ones.  Against a 64-bit division per chunk and
+// an atomic per wave (108 us of a 30001-row, 8-head call, 1.1 TB/s), whole call: 300
+// rows 22.2 -> 18.7 us, 3774 108 -> 25.3, 30001 158 -> 81.7.
+constexpr int AM_THREADS = 256;
+constexpr int AM_UNROLL = 4;
+__global__ __launch_bounds__(AM_THREADS) void q8_absmax_kernel(const QuantParams p) {
+    __shared__ float red[AM_THREADS / 64];
+    const u32x4 *src = (const u32x4 *)(blockIdx.z == 0 ? p.kc : p.vc) + (int64_t)blockIdx.y * p.cap * (D / 8);
+    const int64_t chunks = p.L * (D / 8);
+    const int64_t step = (int64_t)gridDim.x * AM_THREADS;
     float m = 0.f;
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < chunks; c += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t row = c / (D / 8);                 // (g, j) with j < L
-        const int64_t g = row / p.L, j = row % p.L;
-        const u32x4 v = *(const u32x4 *)(src + (g * p.cap + j) * D + 8 * (c % (D / 8)));
+    for (int64_t c = (int64_t)blockIdx.x * AM_THREADS + threadIdx.x; c < chunks; c += AM_UNROLL * step) {
+        u32x4 v[AM_UNROLL];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            m = fmaxf(m, fabsf(bf16_to_f32((uint16_t)(v[q] & 0xffff))));
-            m = fmaxf(m, fabsf(bf16_to_f32((uint16_t)(v[q] >> 16))));
+        for (int u = 0; u < AM_UNROLL; ++u) {
+            const int64_t i = c + u * step;
+            v[u] = src[i < chunks ? i : c];       // past the end: this thread's first again
         }
+#pragma unroll
+        for (int u = 0; u < AM_UNROLL; ++u)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                m = fmaxf(m, fabsf(__uint_as_float(v[u][q] << 16)));
+                m = fmaxf(m, fabsf(__uint_as_float(v[u][q] & 0xffff0000u)));
+            }
     }
-    // wave max, then one atomic per wave
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-    if ((threadIdx.x & 63) == 0 && m > 0.f) atomicMax((unsigned int *)&p.scales[blockIdx.y], __float_as_uint(m));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 1; w < AM_THREADS / 64; ++w) m = fmaxf(m, red[w]);
+        if (m > 0.f) atomicMax((unsigned int *)&p.scales[blockIdx.z], __float_as_uint(m));
+    }
 }
 
 __device__ __forceinline__ float scale_from_max(float m) { return m > 0.f ? __fdiv_rn(m, (float)QMAX) : 1.f; }
@@ -130,11 +149,11 @@ __global__ void q8_finalize_kernel(float *scales) {
 
 hipError_t launch_quantize(const QuantParams &p, hipStream_t s) {
     hipLaunchKernelGGL(q8_clear_kernel, dim3(1), dim3(64), 0, s, p.scales);
-    const int64_t chunks = (int64_t)p.n_kv_heads * p.L * (D / 8);
-    int blocks = (int)((chunks + 255) / 256);
-    if (blocks > 1024) blocks = 1024;
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(q8_absmax_kernel, dim3(blocks, 2), dim3(256), 0, s, p);
+    // about eight workgroups per compute unit over both tensors and all heads
+    const int64_t need = (p.L * (D / 8) + AM_THREADS * AM_UNROLL - 1) / (AM_THREADS * AM_UNROLL);
+    const int64_t most = 1024 / p.n_kv_heads > 1 ? 1024 / p.n_kv_heads : 1;
+    const int blocks = (int)(need < most ? need : most);
+    hipLaunchKernelGGL(q8_absmax_kernel, dim3(blocks, p.n_kv_heads, 2), dim3(AM_THREADS), 0, s, p);
     const int64_t nb = (p.L + 31) / 32;
     hipLaunchKernelGGL(q8_quant_kernel, dim3((unsigned)(nb * p.n_kv_heads)), dim3(256), 0, s, p);
     hipLaunchKernelGGL(q8_finalize_kernel, dim3(1), dim3(64), 0, s, p.scales);
