@@ -124,7 +124,9 @@ def make_desc(n_q_heads, n_kv_heads, head_dim, dtype, capacity, scale=0.0):
 
 def _stream(stream):
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        # the handle of torch.cuda.current_stream() without building a Stream object
+        # (2.8 us of a small call's 11 us on the host; 0.3 this way)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
@@ -140,7 +142,7 @@ def _check(t, name, desc, shape):
         raise ValueError("%s has dtype %s, the layer descriptor says %s" % (name, t.dtype, want))
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape and tuple(t.shape) != tuple(shape):
         raise ValueError("%s has shape %s, expected %s" % (name, tuple(t.shape), tuple(shape)))
     return t.data_ptr()
 
@@ -240,10 +242,13 @@ def kvr_cache_append(desc, Ks, Vs, S, kcache, vcache, L_cur, stream=None):
            "kvr_cache_append")
 
 
+_SIZE_ERR = ctypes.c_size_t(-1).value   # a kvr_*_bytes call's answer to invalid arguments
+
+
 def kvr_q8_bytes(desc):
     """Bytes of each int8 artifact tensor (kq, vq) for this descriptor."""
     nb = load().kvr_q8_bytes(ctypes.byref(desc))
-    if nb == ctypes.c_size_t(-1).value:
+    if nb == _SIZE_ERR:
         raise ValueError("invalid layer descriptor")
     return nb
 
