@@ -232,17 +232,23 @@ __device__ __forceinline__ void build_x(const GemvParams &p, uint16_t *xs, float
 // N..2N-1; a wave takes the pair (n, N + n) and stores act[n] =
 // silu(g) * u with g and u rounded to the element format first, as the
 // multi-row path rounds them before silu_mul_kernel.
-template <class E, int PRO, int RW, int PAIR = 0>
+// U: k-steps (512 elements) per block of loads, see two_row_steps.  HBM bounds it: the
+// registers of a step are refilled as soon as its multiply-adds are issued, so that a
+// wave has U steps of both rows in flight throughout.  With a block copied aside while
+// the next one loads (128 registers; K = 2560 as blocks of four and of one step) the
+// gate and up product of 99.6 MB took 20.5 us in a one-token step, this way 16.7 to
+// 17.5; three workgroups per compute unit, or one, cost the 12-layer step 2 %, ten waves
+// per workgroup as well.
+template <class E, int PRO, int RW, int PAIR, int U>
 __global__ __launch_bounds__(GT) void gemv_kernel(const GemvParams p) {
     static_assert(!PAIR || RW == 2, "a pair is two rows");
     __shared__ __attribute__((aligned(16))) uint16_t xs[kGemvMaxK];
     __shared__ float red[GT / 64];
-    constexpr int U = RW == 1 ? 8 : 4;                   // k-steps per block of loads
     constexpr int NW = GT / 64;
     constexpr int RPW = PAIR ? 1 : RW;                   // outputs per wave and step
     const int tid = threadIdx.x;
     const int KC = p.K / 8;
-    const int wave = tid >> 6, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;   // row addresses in SGPRs
     const int steps = (KC + 63) / 64;
     // wave w of workgroup b takes row groups (b * NW + w) * RPW, then every
     // grid-stride after it: each workgroup builds x' once for all its rows
@@ -252,20 +258,18 @@ __global__ __launch_bounds__(GT) void gemv_kernel(const GemvParams p) {
     // Every load is issued, from a clamped (valid) address: without branches
     // the compiler counts the loads in flight and waits only for the block it
     // uses.  Chunks past K and rows past N are loaded and never used.
-    auto load_block = [&](int64_t nb, int s0) {
+    auto load_step = [&](int u, int64_t nb, int s0) {
+        const uint32_t at = 16u * (uint32_t)min(lane + 64 * (s0 + u), KC - 1);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int c = min(lane + 64 * (s0 + u), KC - 1);
-#pragma unroll
-            for (int r = 0; r < RW; ++r) {
-                const int64_t row = PAIR ? (nb < p.N ? nb : p.N - 1) + r * p.N
-                                         : (nb + r < p.N ? nb + r : p.N - 1);
-                wv[u][r] = *(const u32x4 *)(p.w + row * p.K + 8 * c);
-            }
+        for (int r = 0; r < RW; ++r) {
+            const int64_t row = PAIR ? (nb < p.N ? nb : p.N - 1) + r * p.N
+                                     : (nb + r < p.N ? nb + r : p.N - 1);
+            wv[u][r] = *(const u32x4 *)((const char *)(p.w + row * p.K) + at);
         }
     };
     // the first weights do not depend on x: in flight while the prologue runs
-    load_block(n0, 0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) load_step(u, n0, 0);
 
     build_x<E, PRO, GT>(p, xs, red, tid);
     __syncthreads();
@@ -276,15 +280,11 @@ __global__ __launch_bounds__(GT) void gemv_kernel(const GemvParams p) {
 #pragma unroll
         for (int r = 0; r < RW; ++r) acc[r] = 0.f;
         for (int s0 = 0; s0 < steps; s0 += U) {
-            u32x4 cur[U][RW];
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int r = 0; r < RW; ++r) cur[u][r] = wv[u][r];
-            // the next block streams in meanwhile: of this row group, or the
-            // first of the next one
-            if (s0 + U < steps) load_block(n0, s0 + U);
-            else load_block(n0 + stride, 0);
+            // each step's registers are refilled as soon as it is done: the next block's,
+            // of this row group, or the first of the next one
+            const bool more = s0 + U < steps;
+            const int64_t n_next = more ? n0 : n0 + stride;
+            const int s_next = more ? s0 + U : 0;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int c = lane + 64 * (s0 + u);
@@ -294,10 +294,11 @@ __global__ __launch_bounds__(GT) void gemv_kernel(const GemvParams p) {
                     for (int r = 0; r < RW; ++r)
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            acc[r] = __builtin_fmaf(E::lo(cur[u][r][i]), E::lo(xv[i]), acc[r]);
-                            acc[r] = __builtin_fmaf(E::hi(cur[u][r][i]), E::hi(xv[i]), acc[r]);
+                            acc[r] = __builtin_fmaf(E::lo(wv[u][r][i]), E::lo(xv[i]), acc[r]);
+                            acc[r] = __builtin_fmaf(E::hi(wv[u][r][i]), E::hi(xv[i]), acc[r]);
                         }
                 }
+                load_step(u, n_next, s_next);
             }
         }
 #pragma unroll
@@ -453,6 +454,11 @@ int linear(Blas *bl, int32_t dtype, const void *x, const void *w, int64_t rows, 
     return st == HIPBLAS_STATUS_SUCCESS ? KVR_OK : KVR_ERR_DEVICE;
 }
 
+// k-steps per block of a wave that reads two rows: the loads past K in a row's last
+// block are issued all the same, so the fewer of them (K = 2560 is five steps: one
+// block of five, or one of four and one of a single useful step).
+int two_row_steps(int steps) { return (steps + 4) / 5 * 5 < (steps + 3) / 4 * 4 ? 5 : 4; }
+
 // One-row product: up to kGemv1MaxRows outputs with rows of at most
 // kGemv1MaxSteps loads per lane, one row per wave and all loads at once;
 // otherwise at most kGemvMaxGrid workgroups of GT threads, one row per wave and
@@ -499,8 +505,9 @@ int gemv(int32_t dtype, int pro, const void *x, const void *ln, float eps, const
     const int rw = N >= 65536 ? 2 : 1;
     const int64_t groups = (N + rw * (GT / 64) - 1) / (rw * (GT / 64));
     const dim3 grid((unsigned)(groups < kGemvMaxGrid ? groups : kGemvMaxGrid));
-#define KVR_GEMV(E_, P_, R_) hipLaunchKernelGGL((gemv_kernel<E_, P_, R_>), grid, dim3(GT), 0, s, g)
-#define KVR_GEMV_RW(E_, P_) do { if (rw == 2) KVR_GEMV(E_, P_, 2); else KVR_GEMV(E_, P_, 1); } while (0)
+#define KVR_GEMV(E_, P_, R_, U_) hipLaunchKernelGGL((gemv_kernel<E_, P_, R_, 0, U_>), grid, dim3(GT), 0, s, g)
+#define KVR_GEMV_RW(E_, P_) do { if (rw == 1) KVR_GEMV(E_, P_, 1, 8); else if (two_row_steps(steps) == 5) KVR_GEMV(E_, P_, 2, 5); \
+                                 else KVR_GEMV(E_, P_, 2, 4); } while (0)
 #define KVR_GEMV_PRO(E_) do { if (pro == kNorm) KVR_GEMV_RW(E_, kNorm); else if (pro == kSilu) KVR_GEMV_RW(E_, kSilu); \
                               else KVR_GEMV_RW(E_, kPlain); } while (0)
     if (dtype == KVR_F16) KVR_GEMV_PRO(F16);
@@ -526,8 +533,11 @@ int gemv_gate_up(int32_t dtype, const void *x, const void *ln, float eps, const 
     g.eps = eps;
     const int64_t groups = (I + GT / 64 - 1) / (GT / 64);
     const dim3 grid((unsigned)(groups < kGemvMaxGrid ? groups : kGemvMaxGrid));
-    if (dtype == KVR_F16) hipLaunchKernelGGL((gemv_kernel<F16, kNorm, 2, 1>), grid, dim3(GT), 0, s, g);
-    else hipLaunchKernelGGL((gemv_kernel<Bf16, kNorm, 2, 1>), grid, dim3(GT), 0, s, g);
+#define KVR_PAIR(E_, U_) hipLaunchKernelGGL((gemv_kernel<E_, kNorm, 2, 1, U_>), grid, dim3(GT), 0, s, g)
+    const bool five = two_row_steps((K / 8 + 63) / 64) == 5;
+    if (dtype == KVR_F16) { if (five) KVR_PAIR(F16, 5); else KVR_PAIR(F16, 4); }
+    else { if (five) KVR_PAIR(Bf16, 5); else KVR_PAIR(Bf16, 4); }
+#undef KVR_PAIR
     return hipGetLastError() == hipSuccess ? KVR_OK : KVR_ERR_DEVICE;
 }
 
