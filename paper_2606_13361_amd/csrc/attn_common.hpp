@@ -273,6 +273,12 @@ __device__ __forceinline__ void dma16_s(uint64_t base, uint32_t off, const void 
     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "m0");
 }
 
+// The same with the non-temporal hint, for bytes that nobody reads again soon
+__device__ __forceinline__ void dma16_s_nt(uint64_t base, uint32_t off, const void *lds_dst) {
+    const uint32_t lds = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)lds_dst;
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(off), "s"(base) : "m0");
+}
+
 // dma16_s for one instruction under the exec mask when `on` is nonzero, and
 // with no lane enabled (nothing loaded, nothing written) when it is zero; `on`
 // must be wave-uniform.  exec is restored inside the statement.

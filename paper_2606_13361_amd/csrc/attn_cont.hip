@@ -247,8 +247,10 @@ __device__ __forceinline__ void codes_to_bf16(const u32x4 w, u32x4 &lo, u32x4 &h
 // are scaled by s_K inside the softmax exponent, the cached part of O by s_V
 // before the first new key (or at the end); the new rows stay bf16.  Cached
 // and new keys then never share a stage.
-// FUSE: q and the new keys arrive unrotated (see above).
-template <int NCT, bool Q8, class E, bool FUSE = false>
+// FUSE: q and the new keys arrive unrotated (see above).  NT: stages of cached bf16
+// rows are loaded with the non-temporal hint (an instance of its own: as a branch on
+// an argument it cost calls over short prefixes 1.5 %).
+template <int NCT, bool Q8, class E, bool FUSE = false, bool NT = false>
 __global__ __launch_bounds__(THREADS) void attn_cont_kernel(const AttnParams p) {
     static_assert(!(Q8 && FUSE), "the int8 artifact's callers rotate their rows");
     static_assert(!Q8 || std::is_same<E, Bf16>::value, "the int8 artifact is a bf16 model's");
@@ -340,9 +342,15 @@ __global__ __launch_bounds__(THREADS) void attn_cont_kernel(const AttnParams p) 
         if (!Q8 && key0 + SKEYS <= cache_end) {
             const uint64_t kb_ = kc_a + (uint64_t)key0 * ROWB, vb_ = vc_a + (uint64_t)key0 * ROWB;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) dma16_s(kb_, off_c[i], kd + 1024 * i);
+            for (int i = 0; i < 8; ++i) {
+                if (NT) dma16_s_nt(kb_, off_c[i], kd + 1024 * i);
+                else dma16_s(kb_, off_c[i], kd + 1024 * i);
+            }
 #pragma unroll
-            for (int i = 0; i < 8; ++i) dma16_s(vb_, off_c[i], vd + 1024 * i);
+            for (int i = 0; i < 8; ++i) {
+                if (NT) dma16_s_nt(vb_, off_c[i], vd + 1024 * i);
+                else dma16_s(vb_, off_c[i], vd + 1024 * i);
+            }
         } else {
             // prefix/new boundary, new rows or a ragged end: per-row source;
             // rows past ke clamp to a valid row (beyond every causal bound, masked)
@@ -680,21 +688,26 @@ __global__ __launch_bounds__(THREADS) void attn_cont_kernel(const AttnParams p) 
 
 }  // namespace
 
-template <bool Q8, class E, bool FUSE = false>
+template <bool Q8, class E, bool FUSE, bool NT>
 void launch_nct(const AttnParams &p, int ncol_tiles, int grid, hipStream_t s) {
     switch (ncol_tiles) {
-        case 1: hipLaunchKernelGGL((attn_cont_kernel<1, Q8, E, FUSE>), dim3(grid), dim3(THREADS), 0, s, p); break;
-        case 2: hipLaunchKernelGGL((attn_cont_kernel<2, Q8, E, FUSE>), dim3(grid), dim3(THREADS), 0, s, p); break;
-        default: hipLaunchKernelGGL((attn_cont_kernel<3, Q8, E, FUSE>), dim3(grid), dim3(THREADS), 0, s, p); break;
+        case 1: hipLaunchKernelGGL((attn_cont_kernel<1, Q8, E, FUSE, NT>), dim3(grid), dim3(THREADS), 0, s, p); break;
+        case 2: hipLaunchKernelGGL((attn_cont_kernel<2, Q8, E, FUSE, NT>), dim3(grid), dim3(THREADS), 0, s, p); break;
+        default: hipLaunchKernelGGL((attn_cont_kernel<3, Q8, E, FUSE, NT>), dim3(grid), dim3(THREADS), 0, s, p); break;
     }
+}
+template <class E, bool FUSE>
+void launch_16(const AttnParams &p, int ncol_tiles, int grid, hipStream_t s) {
+    if (p.stream_kv) launch_nct<false, E, FUSE, true>(p, ncol_tiles, grid, s);
+    else launch_nct<false, E, FUSE, false>(p, ncol_tiles, grid, s);
 }
 
 hipError_t launch_attn_cont(const AttnParams &p, int ncol_tiles, bool q8, bool f16, int grid, hipStream_t s) {
-    if (q8) launch_nct<true, Bf16>(p, ncol_tiles, grid, s);
-    else if (p.rope && f16) launch_nct<false, F16, true>(p, ncol_tiles, grid, s);
-    else if (p.rope) launch_nct<false, Bf16, true>(p, ncol_tiles, grid, s);
-    else if (f16) launch_nct<false, F16>(p, ncol_tiles, grid, s);
-    else launch_nct<false, Bf16>(p, ncol_tiles, grid, s);
+    if (q8) launch_nct<true, Bf16, false, false>(p, ncol_tiles, grid, s);
+    else if (p.rope && f16) launch_16<F16, true>(p, ncol_tiles, grid, s);
+    else if (p.rope) launch_16<Bf16, true>(p, ncol_tiles, grid, s);
+    else if (f16) launch_16<F16, false>(p, ncol_tiles, grid, s);
+    else launch_16<Bf16, false>(p, ncol_tiles, grid, s);
     return hipGetLastError();
 }
 

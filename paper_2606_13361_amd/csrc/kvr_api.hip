@@ -343,6 +343,18 @@ bool use_keys_split(const kvr_desc *d, int64_t n_prefix, int64_t n_tok, const Sp
     return (int64_t)(d->n_q_heads / d->n_kv_heads) * n_tok <= 32 || keys_per_wg > kRowsSplitMaxKeys;
 }
 
+// The keys-split kernel's cached rows are read once per call; loaded with the
+// non-temporal hint they come faster from HBM, but are not found in the last-level
+// cache (256 MB) by a repeated call.  A model's decode step reads every layer's cache
+// before it comes back to the first: from this many bytes on the hint pays there (36
+// layers: over 16391 rows 678 -> 623 us, 1000 rows 393 -> 369, 600 rows 329 -> 321;
+// over 512 rows, 2 MB a layer, 371 -> 378, over 256 269 -> 285), and costs one layer's
+// calls repeated on a cache that fits little (one token over 3774 rows 11.9 -> 12.1,
+// eight over 20000 18.7 -> 19.0; 24 over 32000, which don't fit, 39.0 -> 35.2).  The
+// row-split kernel (24 tokens over 16384 rows 23.6 -> 25.7) and the int8 artifact
+// (24 over 30001 32.3 -> 32.7) do without.
+constexpr int64_t kStreamBytes = 9 << 18;   // K and V rows of the prefix, all kv heads
+
 // Whether the attention kernel of a continuation rotates its rows itself.
 bool fuse_rope(const kvr_desc *d, int64_t n_prefix, int64_t n_tok, const Split &sp) {
     return use_cont(d, n_tok) && n_tok <= kFusedTokens && use_keys_split(d, n_prefix, n_tok, sp);
@@ -411,6 +423,7 @@ int launch_single(const kvr_desc *d, int mode, const void *Q, const void *K, con
     hipError_t e;
     if (mode == kModeContinue && use_cont(d, n_tok)) {
         const int nct = (int)((rows + 31) / 32);
+        p.stream_kv = n_prefix * d->n_kv_heads * d->head_dim * 4 >= kStreamBytes;
         if (append) {            // both kernels store the new rows themselves
             p.kc_app = kc;
             p.vc_app = vc;

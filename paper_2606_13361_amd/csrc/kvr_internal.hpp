@@ -67,6 +67,7 @@ struct AttnParams {
     int64_t q_tok_stride;  // elements between tokens of q (keys-split kernel, with rope)
     int32_t row_tile;    // fp32 path: query rows per workgroup, 16 or 32
     int32_t split_keys;  // 16-bit prefill: 1 runs the key-split kernel (row tiles of kRowsPK)
+    int32_t stream_kv;   // keys-split kernel: 1 runs the instance that loads cached rows with the non-temporal hint
 };
 
 struct AppendParams {
