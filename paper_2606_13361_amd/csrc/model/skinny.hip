@@ -130,6 +130,14 @@ __device__ __forceinline__ void finish(const SkinnyParams &p, const f32x4 *buf, 
     }
 }
 
+// dma16 with the non-temporal hint: a layer's weights are read once and come back
+// after more bytes than any cache holds (a decoder layer over 24 tokens 81.4 -> 74.5
+// us with it, over 5 tokens 67.9 -> 63.3, over 40 90.7 -> 82.9).
+__device__ __forceinline__ void dma16_nt(const void *src, const void *lds_dst) {
+    const uint32_t lds = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)lds_dst;
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds), "v"(src) : "m0");
+}
+
 // Two loads of a weight stage: lane -> row 8 i + lane / 8, slot lane % 8
 template <bool PAIR>
 struct WSrc {
@@ -143,7 +151,7 @@ struct WSrc {
     }
     __device__ __forceinline__ void load(int stage, const unsigned char *dst) const {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) dma16((const void *)(a[i] + (uint64_t)stage * 128), dst + 1024 * i);
+        for (int i = 0; i < 2; ++i) dma16_nt((const void *)(a[i] + (uint64_t)stage * 128), dst + 1024 * i);
     }
 };
 
@@ -271,7 +279,10 @@ __global__ __launch_bounds__(64 * SWV) void skinny_split_kernel(const SkinnyPara
         if (i >= total) return;
         unsigned char *d = slots + (i % NR) * SLOT;
 #pragma unroll
-        for (int u = 0; u < PER; ++u) dma16((const void *)(a[u] + (uint64_t)i * 128), d + 1024 * u);
+        for (int u = 0; u < PER; ++u) {
+            if (u < 2 * RT) dma16_nt((const void *)(a[u] + (uint64_t)i * 128), d + 1024 * u);
+            else dma16((const void *)(a[u] + (uint64_t)i * 128), d + 1024 * u);
+        }
     };
     for (int i = 0; i < NR - 1; ++i) issue(i);
     f32x4 acc[RT][CT];
