@@ -26,6 +26,10 @@
 // stores that quarter of the workgroup's split partial -- or of the output
 // when there is no split.
 //
+// HBM bounds it (a decode step over 16391 rows moves 67 MB in 16.9 us); calls over long
+// prefixes load the cached rows with the non-temporal hint (the host's rule and both
+// sides' times stand at kStreamBytes in kvr_api.hip).
+//
 // LDS tile layout as in the two-group kernel: 256-byte rows, 16-byte chunk c of
 // row r in slot c ^ swz(r), conflict-free for the K reads and the
 // transposing V reads.

@@ -120,7 +120,7 @@ hipError_t launch_attn_rows(const AttnParams &p, bool f16, int grid, hipStream_t
 hipError_t launch_attn_cont(const AttnParams &p, int ncol_tiles, bool q8, bool f16, int grid, hipStream_t s);
 // int8 artifact
 hipError_t launch_quantize(const QuantParams &p, hipStream_t s);
-// fp32 path (VALU), D in {64, 128}
+// fp32 path (fp32 matrix instructions), D in {64, 128}
 hipError_t launch_attn_f32(const AttnParams &p, int head_dim, int grid, hipStream_t s);
 // cache write
 hipError_t launch_append(const AppendParams &p, hipStream_t s);
