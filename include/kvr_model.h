@@ -74,7 +74,8 @@ typedef struct {
 int kvr_blas_create(void **blas);
 int kvr_blas_destroy(void *blas);
 
-/* hipBLASLt workspace bytes every product of this library may use. */
+/* hipBLASLt workspace bytes every product of this library may use; algorithms
+ * that need more are not taken. */
 #define KVR_BLAS_WORKSPACE_BYTES ((size_t)32 << 20)
 
 /*

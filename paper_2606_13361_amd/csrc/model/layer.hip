@@ -2,15 +2,12 @@
 // (include/kvr_model.h).  Normalizations, the per-head q/k normalization with
 // the rotary embedding, the gated activation and the one-row products of a
 // one-token step are kernels of this file; the matrix products of more rows
-// go to hipBLASLt; the attention is libkvr's public entry points.
-#include <hipblaslt/hipblaslt.h>
+// go to hipBLASLt (blas.hip); the attention is libkvr's public entry points.
 #include <math.h>
 #include <string.h>
 
-#include <map>
-#include <tuple>
-
 #include "attn_common.hpp"
+#include "blas.hpp"
 #include "kvr_model.h"
 #include "silu.hpp"
 #include "skinny.hpp"
@@ -398,63 +395,15 @@ bool is16(int32_t dt) { return dt == KVR_BF16 || dt == KVR_F16; }
 size_t up256(size_t b) { return (b + 255) / 256 * 256; }
 
 // ---------------------------------------------------------------- products
-struct Blas {
-    hipblasLtHandle_t h = nullptr;
-    // (rows, n_in, n_out, beta != 0, dtype) -> algorithm
-    std::map<std::tuple<int64_t, int32_t, int32_t, int, int32_t>, hipblasLtMatmulAlgo_t> algos;
-};
-
-struct Gemm {
-    hipblasLtMatmulDesc_t op = nullptr;
-    hipblasLtMatrixLayout_t a = nullptr, b = nullptr, c = nullptr;
-    ~Gemm() {
-        if (a) hipblasLtMatrixLayoutDestroy(a);
-        if (b) hipblasLtMatrixLayoutDestroy(b);
-        if (c) hipblasLtMatrixLayoutDestroy(c);
-        if (op) hipblasLtMatmulDescDestroy(op);
-    }
-};
-
 int gemv(int32_t dtype, int pro, const void *x, const void *ln, float eps, const void *w, int32_t K, int64_t N,
          int beta, void *y, hipStream_t s);
 
-// y = x w^T (+ y): in column-major terms y^T [n_out x rows] = w^T [n_out x n_in]
-// (w stored as an n_in x n_out column-major matrix, transposed) times
-// x^T [n_in x rows].
+// y = x w^T (+ y); ws: KVR_BLAS_WORKSPACE_BYTES.
 int linear(Blas *bl, int32_t dtype, const void *x, const void *w, int64_t rows, int32_t n_in, int32_t n_out,
-           float beta, void *y, void *ws, size_t ws_bytes, hipStream_t s) {
+           float beta, void *y, void *ws, hipStream_t s) {
     if (rows == 1 && n_in <= kGemvMaxK)
         return gemv(dtype, kPlain, x, nullptr, 0.f, w, n_in, n_out, beta != 0.f ? 1 : 0, y, s);
-    const hipDataType ty = dtype == KVR_F16 ? HIP_R_16F : HIP_R_16BF;
-    Gemm g;
-    if (hipblasLtMatmulDescCreate(&g.op, HIPBLAS_COMPUTE_32F, HIP_R_32F) != HIPBLAS_STATUS_SUCCESS)
-        return KVR_ERR_DEVICE;
-    const int32_t ta = HIPBLAS_OP_T, tb = HIPBLAS_OP_N;
-    hipblasLtMatmulDescSetAttribute(g.op, HIPBLASLT_MATMUL_DESC_TRANSA, &ta, sizeof ta);
-    hipblasLtMatmulDescSetAttribute(g.op, HIPBLASLT_MATMUL_DESC_TRANSB, &tb, sizeof tb);
-    if (hipblasLtMatrixLayoutCreate(&g.a, ty, n_in, n_out, n_in) != HIPBLAS_STATUS_SUCCESS ||
-        hipblasLtMatrixLayoutCreate(&g.b, ty, n_in, rows, n_in) != HIPBLAS_STATUS_SUCCESS ||
-        hipblasLtMatrixLayoutCreate(&g.c, ty, n_out, rows, n_out) != HIPBLAS_STATUS_SUCCESS)
-        return KVR_ERR_DEVICE;
-    const auto key = std::make_tuple(rows, n_in, n_out, beta != 0.f ? 1 : 0, dtype);
-    auto it = bl->algos.find(key);
-    if (it == bl->algos.end()) {
-        hipblasLtMatmulPreference_t pref;
-        if (hipblasLtMatmulPreferenceCreate(&pref) != HIPBLAS_STATUS_SUCCESS) return KVR_ERR_DEVICE;
-        const uint64_t wsb = KVR_BLAS_WORKSPACE_BYTES;
-        hipblasLtMatmulPreferenceSetAttribute(pref, HIPBLASLT_MATMUL_PREF_MAX_WORKSPACE_BYTES, &wsb, sizeof wsb);
-        hipblasLtMatmulHeuristicResult_t res;
-        int n = 0;
-        const hipblasStatus_t st =
-            hipblasLtMatmulAlgoGetHeuristic(bl->h, g.op, g.a, g.b, g.c, g.c, pref, 1, &res, &n);
-        hipblasLtMatmulPreferenceDestroy(pref);
-        if (st != HIPBLAS_STATUS_SUCCESS || n < 1) return KVR_ERR_DEVICE;
-        it = bl->algos.emplace(key, res.algo).first;
-    }
-    const float alpha = 1.f;
-    const hipblasStatus_t st = hipblasLtMatmul(bl->h, g.op, &alpha, w, g.a, x, g.b, &beta, y, g.c, y, g.c,
-                                               &it->second, ws, ws_bytes, s);
-    return st == HIPBLAS_STATUS_SUCCESS ? KVR_OK : KVR_ERR_DEVICE;
+    return blas_linear(bl, dtype, x, w, rows, n_in, n_out, beta, y, ws, s);
 }
 
 // k-steps per block of a wave that reads two rows: the loads past K in a row's last
@@ -619,7 +568,7 @@ int kvr_linear(void *blas, int32_t dtype, const void *x, const void *w, int64_t 
     if (!blas || !x || !w || !y || !ws) return KVR_ERR_NULL;
     if (ws_bytes < KVR_BLAS_WORKSPACE_BYTES) return KVR_ERR_WORKSPACE;
     if (!aligned16(x) || !aligned16(w) || !aligned16(y) || !aligned16(ws)) return KVR_ERR_ALIGN;
-    return linear((Blas *)blas, dtype, x, w, rows, n_in, n_out, beta, y, ws, ws_bytes, (hipStream_t)stream);
+    return linear((Blas *)blas, dtype, x, w, rows, n_in, n_out, beta, y, ws, (hipStream_t)stream);
 }
 
 int kvr_rmsnorm(int32_t dtype, const void *x, const void *w, int64_t rows, int32_t n, float eps, void *y,
@@ -713,7 +662,7 @@ int kvr_layer_forward(const kvr_desc *desc, const kvr_layer_shape *shape, const 
             return KVR_ERR_DEVICE;
     } else {
         if ((st = kvr_rmsnorm(dt, h, w->ln1, T, H, shape->eps, b + lw.xn, stream))) return st;
-        if ((st = linear(bl, dt, b + lw.xn, w->wqkv, T, H, Wq, 0.f, b + lw.qkv, blws, KVR_BLAS_WORKSPACE_BYTES, s)))
+        if ((st = linear(bl, dt, b + lw.xn, w->wqkv, T, H, Wq, 0.f, b + lw.qkv, blws, s)))
             return st;
     }
     if (L_prefix > 0 && kvr::fused_rows_ok(desc, L_prefix, T)) {
@@ -767,7 +716,7 @@ int kvr_layer_forward(const kvr_desc *desc, const kvr_layer_shape *shape, const 
             return KVR_ERR_DEVICE;
         return KVR_OK;
     }
-    if ((st = linear(bl, dt, b + lw.att, w->wo, T, Hq * D, H, 1.f, h, blws, KVR_BLAS_WORKSPACE_BYTES, s)))
+    if ((st = linear(bl, dt, b + lw.att, w->wo, T, Hq * D, H, 1.f, h, blws, s)))
         return st;
     // MLP block
     if (one) {
@@ -775,7 +724,7 @@ int kvr_layer_forward(const kvr_desc *desc, const kvr_layer_shape *shape, const 
         return gemv(dt, kPlain, b + lw.act, nullptr, 0.f, w->wd, I, H, 1, h, s);
     }
     if ((st = kvr_rmsnorm(dt, h, w->ln2, T, H, shape->eps, b + lw.xn, stream))) return st;
-    if ((st = linear(bl, dt, b + lw.xn, w->wgu, T, H, 2 * I, 0.f, b + lw.gu, blws, KVR_BLAS_WORKSPACE_BYTES, s)))
+    if ((st = linear(bl, dt, b + lw.xn, w->wgu, T, H, 2 * I, 0.f, b + lw.gu, blws, s)))
         return st;
     if (dt == KVR_F16)
         hipLaunchKernelGGL(silu_mul_kernel<F16>, dim3(grid_of(T * (I / 8))), dim3(NT), 0, s,
@@ -784,7 +733,7 @@ int kvr_layer_forward(const kvr_desc *desc, const kvr_layer_shape *shape, const 
         hipLaunchKernelGGL(silu_mul_kernel<Bf16>, dim3(grid_of(T * (I / 8))), dim3(NT), 0, s,
                            (const uint16_t *)(b + lw.gu), (uint16_t *)(b + lw.act), T, I);
     if (hipGetLastError() != hipSuccess) return KVR_ERR_DEVICE;
-    return linear(bl, dt, b + lw.act, w->wd, T, I, H, 1.f, h, blws, KVR_BLAS_WORKSPACE_BYTES, s);
+    return linear(bl, dt, b + lw.act, w->wd, T, I, H, 1.f, h, blws, s);
 }
 
 }  // extern "C"
