@@ -221,7 +221,9 @@ ReaderPlan plan_readers(const kvr_desc *d, int64_t L_prefix, int64_t total_S, in
 // 33.8 -> 36.2, 64 over 3774 19.7 -> 26.2, 32 over 9000 (36 splits) 24.5 -> 24.8.
 bool use_pp_long(const kvr_desc *d, int64_t L_prefix, int64_t S, const Split &sp) {
     const int64_t rows = (int64_t)(d->n_q_heads / d->n_kv_heads) * S;
-    if (!use_pp(d) || rows <= kContMaxRows || L_prefix + S >= ((int64_t)1 << 30)) return false;   // 32-bit keys there
+    if (!use_pp(d) || rows <= kContMaxRows) return false;
+    // that kernel's keys, and its key tiles times its splits, are 32-bit
+    if ((L_prefix + S + kKeyTile - 1) / kKeyTile * kMaxSplits > 0x7fffffff) return false;
     const int64_t staged = (rows + kRowsBf16 - 1) / kRowsBf16 * d->n_kv_heads * sp.nsplit;
     return (rows >= kLongRows && L_prefix >= kReaderMinSplitTiles * kKeyTile) ||
            (sp.nsplit > 1 && staged > kTargetWorkgroupsStaged) || sp.nsplit > kLongSplits;

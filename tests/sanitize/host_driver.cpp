@@ -21,6 +21,9 @@ static int g_pp_bad = 0;                       // many-readers launches whose pl
 static int g_pp_split = 0, g_pp_whole = 0;     // many-readers launches checked: split last round or not
 static int64_t g_pp_grid = -1, g_pp_tail0 = -1, g_pp_rows = -1;
 
+static int g_long = 0, g_long_bad = 0, g_long_split = 0;   // long continuations on the two-group kernel
+static size_t g_ws_given = (size_t)1 << 60;                // workspace bytes of the running call, where they are checked
+
 namespace kvr {
 hipError_t launch_attn_bf16(const AttnParams &, int, int, bool, int, hipStream_t) { ++g_launches; return hipErrorUnknown; }
 hipError_t launch_merge_bf16(const MergeParams &, int, bool, hipStream_t) { ++g_launches; return hipErrorUnknown; }
@@ -39,6 +42,18 @@ hipError_t launch_attn_pp(const AttnParams &p, int mode, bool, int grid, hipStre
         if (!ok) ++g_pp_bad;
         ++(ns > 1 ? g_pp_split : g_pp_whole);
         g_pp_grid = grid; g_pp_tail0 = t0; g_pp_rows = p.rows_total;
+    } else if (mode == kModeContinue) {
+        // one reader: every tile whole, or every tile in nsplit shares of at least one
+        // key tile, whose partials fit the workspace of the call; 32-bit products
+        const int64_t ns = p.nsplit, tiles = p.tiles_total, rows = (int64_t)p.group * p.seg_tok0[1];
+        const int64_t key_tiles = (p.n_prefix + p.seg_tok0[1] + kKeyTile - 1) / kKeyTile;
+        bool ok = p.n_seg == 1 && p.seg_tok0[0] == 0 && tiles == (rows + kRowsPP - 1) / kRowsPP && ns >= 1 &&
+                  ns <= kMaxSplits && ns <= p.n_prefix / kKeyTile && ns * key_tiles <= 0x7fffffff &&
+                  p.tail_tile0 == (ns > 1 ? 0 : tiles) && (int64_t)grid == tiles * ns * p.n_kv_heads && rows > kContMaxRows;
+        if (ns > 1) ok = ok && p.ws && p.rows_total == rows && (size_t)ns * p.n_kv_heads * rows * 130 * 4 <= g_ws_given;
+        if (!ok) { ++g_long_bad; fprintf(stderr, "long plan: heads %d/%d rows %ld prefix %ld splits %ld tiles %ld given %zu\n", p.n_q_heads, p.n_kv_heads, (long)rows, (long)p.n_prefix, (long)ns, (long)tiles, g_ws_given); }
+        ++g_long;
+        g_long_split += ns > 1;
     }
     return hipErrorUnknown;
 }
@@ -266,6 +281,34 @@ static void split_plans() {
     if (planned < 50) { fprintf(stderr, "only %d split plans checked\n", planned); ++fails; }
 }
 
+// Continuations of more than 96 rows per kv head, over head counts, lengths and
+// token counts: the plans' invariants (checked in the stubs).
+static void long_plans() {
+    void *P = (void *)(uintptr_t)0x100000;
+    const int heads[][2] = {{32, 8}, {8, 8}, {12, 3}, {64, 8}, {16, 16}, {32, 32}, {4, 1}, {16, 2}, {40, 8}, {28, 4}, {5, 5}, {96, 1}};
+    const int64_t lens[] = {1, 255, 256, 300, 1000, 4000, 16000, 32000, 200000, ((int64_t)1 << 29) - 500, (int64_t)1 << 29,
+                            ((int64_t)1 << 30) - 100, (int64_t)1 << 31};
+    const int64_t rows[] = {97, 128, 129, 256, 257, 600, 1024, 2047, 2048, 2049, 5000, 20000};
+    for (const auto &h : heads)
+        for (int64_t L : lens)
+            for (int64_t r : rows)
+                for (int dt : {KVR_BF16, KVR_F16}) {
+                    const kvr_desc d = desc(h[0], h[1], 128, dt, (int64_t)1 << 32);
+                    const int64_t S = (r * h[1] + h[0] - 1) / h[0];
+                    g_ws_given = kvr_workspace_bytes(&d, L, S, 1);
+                    EXPECT(kvr_continue(&d, P, P, P, P, P, L, S, P, P, g_ws_given, nullptr), KVR_ERR_DEVICE);
+                    g_ws_given = kvr_workspace_bytes(&d, L, S, 1);
+                    if (g_ws_given <= KVR_NOALLOC_SCRATCH_BYTES && g_ws_given == 0)   // no device scratch needed
+                        EXPECT(kvr_continue_noalloc(&d, P, P, P, P, P, L, S, P, nullptr), KVR_ERR_DEVICE);
+                }
+    g_ws_given = (size_t)1 << 60;
+    if (g_long_bad) { fprintf(stderr, "%d long continuations broke a plan invariant\n", g_long_bad); ++fails; }
+    if (g_long_split < 200 || g_long - g_long_split < 100) {
+        fprintf(stderr, "only %d split and %d whole long plans checked\n", g_long_split, g_long - g_long_split);
+        ++fails;
+    }
+}
+
 int main() {
     if (kvr_abi_version() != KVR_ABI_VERSION) {
         fprintf(stderr, "ABI version mismatch\n");
@@ -275,6 +318,7 @@ int main() {
         if (!kvr_strerror(s) || !kvr_strerror(s)[0]) ++fails;
     fixed_cases();
     split_plans();
+    long_plans();
     fuzz();
     if (g_pp_bad) {
         fprintf(stderr, "%d many-readers launches broke a plan invariant\n", g_pp_bad);
