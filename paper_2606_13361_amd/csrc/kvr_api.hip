@@ -39,10 +39,8 @@ constexpr int64_t kReaderMinSplitTiles = 4;
 constexpr double kReaderSplitFixed = 0.07;
 constexpr double kReaderMergeCost = 0.04;
 constexpr double kReaderTileUs = 2.0;
-// A long continuation on the same kernel: from this many query rows per kv head
-// on in any case; fixed time of a workgroup and of the merge launch
-constexpr int64_t kLongRows = 8 * kRowsPP;
-constexpr int64_t kLongSplits = 48;
+// A long continuation on the same kernel: fixed time of a split workgroup and of
+// the merge launch, as its split count is chosen by
 constexpr double kLongSplitFixedUs = 6.0;
 constexpr double kLongMergeUs = 5.0;
 constexpr double kPartialBytesPerUs = 5.0e6;
@@ -205,30 +203,8 @@ ReaderPlan plan_readers(const kvr_desc *d, int64_t L_prefix, int64_t total_S, in
     return r;
 }
 
-// Continuations of more than kContMaxRows query rows per kv head (16-bit,
-// head_dim 128): the two-group kernel, as one reader, or the register-staged
-// one.  Per workgroup the two-group kernel is the faster one (256 rows and a
-// 64-key tile in about 1.7 us, the staged one 2 x 128 rows in about 1.8 us with
-// its last round only part full), but it starts slower (about 10 us of launch,
-// query rows and first tiles) and idles the waves of a partial row tile.  It
-// pays from eight full row tiles per kv head on over a prefix of at least four
-// key tiles, and below that where the staged plan needs a second round of
-// workgroups or so many splits that its merge takes several passes.  Measured, staged ->
-// two-group, 8 kv heads, 4 query heads each: 517 tokens over 7001 129.8 -> 87.5
-// us, 512 over 300 36.0 -> 31.6, 1024 over 1000 71.7 -> 61.0, 2000 over 1000 165
-// -> 87, 300 over 20000 (560 workgroups staged) 188 -> 115, 32 over 20000 (63
-// splits) 40.8 -> 32.9; beyond the line: 600 over 64 22.5 -> 25.6, 256 over 3774
-// 33.8 -> 36.2, 64 over 3774 19.7 -> 26.2, 32 over 9000 (36 splits) 24.5 -> 24.8.
-bool use_pp_long(const kvr_desc *d, int64_t L_prefix, int64_t S, const Split &sp) {
-    const int64_t rows = (int64_t)(d->n_q_heads / d->n_kv_heads) * S;
-    if (!use_pp(d) || rows <= kContMaxRows) return false;
-    // that kernel's keys, and its key tiles times its splits, are 32-bit
-    if ((L_prefix + S + kKeyTile - 1) / kKeyTile * kMaxSplits > 0x7fffffff) return false;
-    const int64_t staged = (rows + kRowsBf16 - 1) / kRowsBf16 * d->n_kv_heads * sp.nsplit;
-    return (rows >= kLongRows && L_prefix >= kReaderMinSplitTiles * kKeyTile) ||
-           (sp.nsplit > 1 && staged > kTargetWorkgroupsStaged) || sp.nsplit > kLongSplits;
-}
-// Its plan: row tiles of kRowsPP rows; fewer workgroups than compute units are
+// A long continuation's plan on the two-group kernel, as one reader: row tiles of
+// kRowsPP rows; fewer workgroups than compute units are
 // split over the keys, all alike.  The partials stay within ws_bytes, what
 // plan_split asked the caller for; the split count is the cheapest within that,
 // costs as for the readers.
@@ -260,6 +236,64 @@ ReaderPlan plan_long(const kvr_desc *d, int64_t L_prefix, int64_t S, size_t ws_b
     r.tail0 = 0;
     r.rows_tail = rows;
     return r;
+}
+
+// Whether a continuation of more than kContMaxRows query rows per kv head (16-bit,
+// head_dim 128) runs on the two-group kernel, with plan_long, or on the
+// register-staged one, with plan_split: the one whose plan is expected to take less
+// time, both counted in 64-key tiles of the workgroup that ends last.  Staged: 5.5 us
+// and 1.65 us a tile, 1.85 us where two workgroups share a compute unit, which takes
+// the 513th and later ones after others.  Two-group (256 rows instead of 128): 9.3
+// us, 8 more for each further round of 256, 1.7 us a tile.  A merge takes 2.5 or 3.5
+// us and its partials' traffic, and more past 32 splits, where it reads them in
+// several passes.  (The constants are a least-squares fit to both kernels' times at
+// 2596 sizes: 12 head counts from 4 / 1 to 32 / 32, 97 to 6000 rows over 130 to 32000 keys; it
+// misses by 7 % rms.)
+// Measured by this rule, 70 of the sizes end more than 2 % behind the staged kernel,
+// the worst 11 %; the mean of all is 0.5 % behind the faster of the two.  Staged ->
+// two-group where it picks the second, 32 / 8 heads: 517 tokens over 7001 129.8 -> 87.5
+// us, 300 over 20000 188 -> 115, 500 over 2000 51.3 -> 44.7, 1024 over 1000 74 -> 60.5;
+// where it stays: 100 over 4000 25.6 (28.2), 300 over 1000 33.7 (33.5), 4 / 1 heads: 512
+// over 300 24.9 (31.1), 64 over 16000 24.2 (28.9).
+// A prefix of fewer than four key tiles leaves nothing to split: staged.
+constexpr double kPreferStaged = 1.02;   // the fit's tie: what ran there before
+bool use_pp_long(const kvr_desc *d, int64_t L_prefix, int64_t S, const Split &sp) {
+    const int64_t G = d->n_q_heads / d->n_kv_heads;
+    const int64_t rows = G * S, keys = L_prefix + S;
+    if (!use_pp(d) || rows <= kContMaxRows || L_prefix < kReaderMinSplitTiles * kKeyTile) return false;
+    // that kernel's keys, and its key tiles times its splits, are 32-bit
+    const int64_t key_tiles = (keys + kKeyTile - 1) / kKeyTile;
+    if (key_tiles * kMaxSplits > 0x7fffffff) return false;
+    const double rec_us = (double)d->n_kv_heads * (double)rows * (d->head_dim + 2) * sizeof(float) / kPartialBytesPerUs;
+    // rounds of `slots` workgroups in front of the last one, and the key tiles it waits for there
+    struct Wait { double rounds, tiles; };
+    auto wait = [&](int64_t wgs, int64_t slots, int64_t splits) {
+        Wait w;
+        w.rounds = (double)((wgs - 1) / slots);
+        // their mean position in the launch: later row tiles see more of the own tokens
+        const double at = 1.0 - (double)slots * (w.rounds + 1.0) / (2.0 * (double)wgs);
+        w.tiles = w.rounds * ((double)L_prefix + (double)S * (at > 0 ? at : 0)) / kKeyTile / (double)splits;
+        return w;
+    };
+    auto merge_us = [&](int64_t splits, double fixed, double many) {
+        return splits > 1 ? fixed + 2.0 * (double)splits * rec_us + (splits > 32 ? many : 0.0) : 0.0;
+    };
+    // staged: the prefix in sp.nsplit chunks, the last one with the own tokens
+    const int64_t sw = (rows + kRowsBf16 - 1) / kRowsBf16 * d->n_kv_heads * sp.nsplit;
+    int64_t chain = key_tiles;
+    if (sp.nsplit > 1) {
+        const int64_t last = keys - (sp.nsplit - 1) * sp.chunk;
+        chain = ((last > sp.chunk ? last : sp.chunk) + kKeyTile - 1) / kKeyTile;
+    }
+    const double s_tile = sw <= kCus ? 1.65 : 1.85;
+    const double staged =
+        5.5 + s_tile * ((double)chain + wait(sw, 2 * kCus, sp.nsplit).tiles) + merge_us(sp.nsplit, 2.5, 5.5);
+    // two-group: equal shares of all key tiles
+    const ReaderPlan lp = plan_long(d, L_prefix, S, sp.ws_bytes);
+    const Wait lw = wait(lp.tiles * d->n_kv_heads * lp.nsplit, kCus, lp.nsplit);
+    const int64_t l_chain = (key_tiles + lp.nsplit - 1) / lp.nsplit;
+    const double two_group = 9.3 + 8.0 * lw.rounds + 1.7 * ((double)l_chain + lw.tiles) + merge_us(lp.nsplit, 3.5, 1.5);
+    return two_group * kPreferStaged < staged;
 }
 
 int to_status(hipError_t e) { return e == hipSuccess ? KVR_OK : KVR_ERR_DEVICE; }

@@ -23,9 +23,12 @@ static int64_t g_pp_grid = -1, g_pp_tail0 = -1, g_pp_rows = -1;
 
 static int g_long = 0, g_long_bad = 0, g_long_split = 0;   // long continuations on the two-group kernel
 static size_t g_ws_given = (size_t)1 << 60;                // workspace bytes of the running call, where they are checked
+static char g_kernel = 0;                                  // the last attention launch: 's'taged, 'p' two-group, ...
 
 namespace kvr {
-hipError_t launch_attn_bf16(const AttnParams &, int, int, bool, int, hipStream_t) { ++g_launches; return hipErrorUnknown; }
+hipError_t launch_attn_bf16(const AttnParams &, int, int mode, bool, int, hipStream_t) {
+    ++g_launches; if (mode == kModeContinue) g_kernel = 's'; return hipErrorUnknown;
+}
 hipError_t launch_merge_bf16(const MergeParams &, int, bool, hipStream_t) { ++g_launches; return hipErrorUnknown; }
 // many readers on the two-group kernel: the packed plan must cover its tiles
 // with whole workgroups (split tiles ns times), and split partial rows must
@@ -54,6 +57,7 @@ hipError_t launch_attn_pp(const AttnParams &p, int mode, bool, int grid, hipStre
         if (!ok) { ++g_long_bad; fprintf(stderr, "long plan: heads %d/%d rows %ld prefix %ld splits %ld tiles %ld given %zu\n", p.n_q_heads, p.n_kv_heads, (long)rows, (long)p.n_prefix, (long)ns, (long)tiles, g_ws_given); }
         ++g_long;
         g_long_split += ns > 1;
+        g_kernel = 'p';
     }
     return hipErrorUnknown;
 }
@@ -282,7 +286,8 @@ static void split_plans() {
 }
 
 // Continuations of more than 96 rows per kv head, over head counts, lengths and
-// token counts: the plans' invariants (checked in the stubs).
+// token counts: the plans' invariants (checked in the stubs), and the route of calls
+// that measured clearly faster on one kernel.
 static void long_plans() {
     void *P = (void *)(uintptr_t)0x100000;
     const int heads[][2] = {{32, 8}, {8, 8}, {12, 3}, {64, 8}, {16, 16}, {32, 32}, {4, 1}, {16, 2}, {40, 8}, {28, 4}, {5, 5}, {96, 1}};
@@ -301,6 +306,34 @@ static void long_plans() {
                     if (g_ws_given <= KVR_NOALLOC_SCRATCH_BYTES && g_ws_given == 0)   // no device scratch needed
                         EXPECT(kvr_continue_noalloc(&d, P, P, P, P, P, L, S, P, nullptr), KVR_ERR_DEVICE);
                 }
+    struct Route { int hq, hkv; int64_t L, S; char want; };
+    const Route routes[] = {
+        // us staged, two-group
+        {4, 1, 300, 512, 's'},      // 24.9, 31.1
+        {4, 1, 16000, 64, 's'},     // 24.2, 28.9
+        {16, 2, 1000, 256, 's'},    // 23.6, 29.9
+        {12, 1, 16384, 24, 's'},    // 21.4, 26.3
+        {12, 3, 16000, 48, 's'},    // 28.0, 30.7
+        {32, 8, 4000, 100, 's'},    // 25.6, 28.2
+        {32, 8, 300, 64, 's'},      // 14.3, 20.0
+        {32, 8, 64, 600, 's'},      // 22.5, 25.6
+        {32, 8, 7001, 517, 'p'},    // 128.9, 87.6
+        {32, 8, 20000, 300, 'p'},   // 187.2, 116.0
+        {32, 8, 2000, 500, 'p'},    // 51.3, 44.7
+        {32, 8, 1000, 1024, 'p'},   // 74.2, 60.5
+        {8, 8, 4000, 768, 'p'},     // 58.5, 38.3
+        {4, 1, 20000, 1500, 'p'},   // 150.9, 80.2
+    };
+    for (const Route &r : routes) {
+        const kvr_desc d = desc(r.hq, r.hkv, 128, KVR_BF16, 40000);
+        g_kernel = 0;
+        g_ws_given = kvr_workspace_bytes(&d, r.L, r.S, 1);
+        EXPECT(kvr_continue(&d, P, P, P, P, P, r.L, r.S, P, P, g_ws_given, nullptr), KVR_ERR_DEVICE);
+        if (g_kernel != r.want) {
+            fprintf(stderr, "%d/%d heads, %ld over %ld: kernel %c, want %c\n", r.hq, r.hkv, (long)r.S, (long)r.L, g_kernel, r.want);
+            ++fails;
+        }
+    }
     g_ws_given = (size_t)1 << 60;
     if (g_long_bad) { fprintf(stderr, "%d long continuations broke a plan invariant\n", g_long_bad); ++fails; }
     if (g_long_split < 200 || g_long - g_long_split < 100) {

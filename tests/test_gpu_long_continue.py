@@ -1,8 +1,8 @@
-"""Continuations on both sides of the line between the register-staged and the
-two-group kernel at head_dim 128: 2048 query rows per kv head (one row less, one
-more), prefixes of 256 keys (one less), a staged plan of more than 512
-workgroups, one of more than 48 splits, group sizes that divide no tile, no
-prefix, and the update and RoPE entry points.  Sampled rows against the fp64
+"""Continuations on the register-staged and the two-group kernel at head_dim 128,
+which a model of both plans' times chooses (the CPU test of the plans names sizes of
+either side): row counts around 2048 per kv head and around a prefix of 256 keys
+(staged), split plans of few and of many key ranges, a plan of whole tiles, group
+sizes that divide no tile, no prefix, and the update and RoPE entry points.  Sampled rows against the fp64
 oracle (1e-2 bf16, 5e-3 fp16); every output row has to be written; two calls
 give the same bits."""
 import numpy as np
@@ -33,6 +33,7 @@ CASES = [
     (5, 5, BF16, 300, 2049, "plain"), (8, 1, BF16, 2500, 300, "append"), (4, 1, BF16, 0, 600, "plain"),
     (16, 4, BF16, 900, 520, "rope"), (12, 12, BF16, 9000, 100, "plain"), (32, 8, BF16, 12800, 25, "plain"),
     (32, 8, F16, 8192, 160, "append"),
+    (5, 5, BF16, 700, 1030, "plain"), (32, 8, BF16, 300, 2001, "append"), (7, 1, F16, 3001, 800, "plain"),
 ]
 
 
