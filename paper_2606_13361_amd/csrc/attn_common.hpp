@@ -71,6 +71,11 @@ struct Bf16 {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(b), c, 0, 0, 0);
     }
     __device__ static __forceinline__ uint32_t pack2(float lo, float hi) { return pack_bf16x2(lo, hi); }
+    // pack2 of values rounded to fp32 first, and of two fused multiply-adds (see F16)
+    __device__ static __forceinline__ uint32_t pack2_f32(float lo, float hi) { return pack2(lo, hi); }
+    __device__ static __forceinline__ uint32_t pack2_fma(float a0, float b0, float c0, float a1, float b1, float c1) {
+        return pack2(__builtin_fmaf(a0, b0, c0), __builtin_fmaf(a1, b1, c1));
+    }
     // the two elements of a packed word, widened exactly
     __device__ static __forceinline__ float lo(uint32_t w) { return __uint_as_float(w << 16); }
     __device__ static __forceinline__ float hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
@@ -85,6 +90,22 @@ struct F16 {
         v[0] = (_Float16)lo;
         v[1] = (_Float16)hi;
         return __builtin_bit_cast(uint32_t, v);
+    }
+    // The compiler folds a conversion of a fused multiply-add into one instruction that
+    // rounds once, to fp16, where it finds it convenient (about one element in 2^13 then
+    // differs).  These two say which it is: rounded to fp32 first, or once.
+    __device__ static __forceinline__ uint32_t pack2_f32(float lo, float hi) {
+        asm("" : "+v"(lo));
+        asm("" : "+v"(hi));
+        return pack2(lo, hi);
+    }
+    __device__ static __forceinline__ uint32_t pack2_fma(float a0, float b0, float c0, float a1, float b1, float c1) {
+        uint32_t w = 0;
+        // (half-register writes need a wait state before the next use)
+        asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[0,0,0]\n\ts_nop 1\n\t"
+            "v_fma_mixhi_f16 %0, %4, %5, %6 op_sel_hi:[0,0,0]\n\ts_nop 1"
+            : "+&v"(w) : "v"(a0), "v"(b0), "v"(c0), "v"(a1), "v"(b1), "v"(c1));
+        return w;
     }
     __device__ static __forceinline__ float lo(uint32_t w) { return (float)__builtin_bit_cast(f16x2, w)[0]; }
     __device__ static __forceinline__ float hi(uint32_t w) { return (float)__builtin_bit_cast(f16x2, w)[1]; }
@@ -122,17 +143,16 @@ __device__ __forceinline__ void rope_rot(float x1, float x2, float c, float s, f
 
 // Rotate 8 + 8 packed elements: lo holds dims i0..i0+7, hi dims i0+d/2..; cs
 // points at the table entries (cos, sin) of dims i0..i0+7 at the row's position.
+// The rotation of rope_rot; lo is rounded once, hi to fp32 first.
 template <class E>
 __device__ __forceinline__ void rope_rot8(u32x4 &lo, u32x4 &hi, const float *cs) {
     const float4 *c4 = (const float4 *)cs;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
         const float4 t = c4[w];        // (cos, sin) of dims 2w and 2w + 1
-        float a1, a2, b1, b2;
-        rope_rot(E::lo(lo[w]), E::lo(hi[w]), t.x, t.y, a1, a2);
-        rope_rot(E::hi(lo[w]), E::hi(hi[w]), t.z, t.w, b1, b2);
-        lo[w] = E::pack2(a1, b1);
-        hi[w] = E::pack2(a2, b2);
+        const float a1 = E::lo(lo[w]), a2 = E::lo(hi[w]), b1 = E::hi(lo[w]), b2 = E::hi(hi[w]);
+        lo[w] = E::pack2_fma(a1, t.x, -(a2 * t.y), b1, t.z, -(b2 * t.w));
+        hi[w] = E::pack2_f32(__builtin_fmaf(a2, t.x, a1 * t.y), __builtin_fmaf(b2, t.z, b1 * t.w));
     }
 }
 

@@ -70,8 +70,8 @@ __device__ __forceinline__ int swz(int row) { return ((row >> 2) & 3) | ((row & 
 
 // Rotation in the kernel, in LDS: eight lanes a row, lane c of them dims 8c ..
 // 8c + 7 and their partners 64 further (the norm's sum of squares meets in the
-// eight), the same operations and rounding as the pre-pass.  fuse_lds: the tokens'
-// table rows; nw: the row's norm weights (read only with p.q_norm).
+// eight).  Without the norm the same operations and rounding as the pre-pass.  fuse_lds:
+// the tokens' table rows; nw: the row's norm weights (read only with p.q_norm).
 template <class E>
 __device__ __forceinline__ void rotate_row(const AttnParams &p, unsigned char *rows, int row, int c, int tk,
                                            const unsigned char *fuse_lds, const unsigned char *nw, u32x4 &lo, u32x4 &hi) {
@@ -101,8 +101,8 @@ __device__ __forceinline__ void rotate_row(const AttnParams &p, unsigned char *r
                      a1, a2);
             rope_rot(E::hi(lo[w]) * inv * E::hi(wl[w]), E::hi(hi[w]) * inv * E::hi(wh[w]), cs[4 * w + 2],
                      cs[4 * w + 3], b1, b2);
-            lo[w] = E::pack2(a1, b1);
-            hi[w] = E::pack2(a2, b2);
+            lo[w] = E::pack2_f32(a1, b1);
+            hi[w] = E::pack2_f32(a2, b2);
         }
     } else {
         rope_rot8<E>(lo, hi, cs);

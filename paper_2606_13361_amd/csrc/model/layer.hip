@@ -94,7 +94,7 @@ __global__ __launch_bounds__(NT) void qk_norm_rope_kernel(const QkParams p) {
     float x1 = act ? E::lo((uint32_t)src[lane]) : 0.f;
     float x2 = act ? E::lo((uint32_t)src[lane + D / 2]) : 0.f;
     auto put = [&](uint16_t *dst, float a, float b) {
-        const uint32_t pk = E::pack2(a, b);
+        const uint32_t pk = E::pack2_f32(a, b);
         dst[lane] = (uint16_t)(pk & 0xffffu);
         dst[lane + D / 2] = (uint16_t)(pk >> 16);
     };
