@@ -141,6 +141,12 @@ __device__ __forceinline__ void rope_rot(float x1, float x2, float c, float s, f
     y2 = __builtin_fmaf(x2, c, x1 * s);
 }
 
+// A rotary pair's part of a head's sum of squares (the q/k norm).  The kernels that
+// normalize heads add the pairs in one order, a butterfly over the pairs' indices from
+// the largest distance to the smallest, so that a token's cached key has the same
+// bits from all of them.
+__device__ __forceinline__ float pair_sq(float x1, float x2) { return __builtin_fmaf(x1, x1, x2 * x2); }
+
 // Rotate 8 + 8 packed elements: lo holds dims i0..i0+7, hi dims i0+d/2..; cs
 // points at the table entries (cos, sin) of dims i0..i0+7 at the row's position.
 // The rotation of rope_rot; lo is rounded once, hi to fp32 first.

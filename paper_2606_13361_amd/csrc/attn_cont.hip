@@ -70,8 +70,9 @@ __device__ __forceinline__ int swz(int row) { return ((row >> 2) & 3) | ((row & 
 
 // Rotation in the kernel, in LDS: eight lanes a row, lane c of them dims 8c ..
 // 8c + 7 and their partners 64 further (the norm's sum of squares meets in the
-// eight).  Without the norm the same operations and rounding as the pre-pass.  fuse_lds:
-// the tokens' table rows; nw: the row's norm weights (read only with p.q_norm).
+// eight), the same operations, rounding and order of sums as the pre-pass of either
+// kind (rope.hip; with the norm qk_norm_rope_kernel).  fuse_lds: the tokens' table
+// rows; nw: the row's norm weights (read only with p.q_norm).
 template <class E>
 __device__ __forceinline__ void rotate_row(const AttnParams &p, unsigned char *rows, int row, int c, int tk,
                                            const unsigned char *fuse_lds, const unsigned char *nw, u32x4 &lo, u32x4 &hi) {
@@ -81,17 +82,28 @@ __device__ __forceinline__ void rotate_row(const AttnParams &p, unsigned char *r
     hi = *ph;
     const float *cs = (const float *)(fuse_lds + tk * CSB) + 16 * c;
     if (p.q_norm) {
-        float ss = 0.f;
+        // pair 8c + e sits in lane c, element e.  Distances 32, 16, 8 are those of lanes
+        // 4, 2, 1 apart, each step leaving a lane the half of its elements whose index
+        // bit equals its own; lane c then holds the sum of elements e = c, and
+        // distances 4, 2, 1 are lanes once more.
+        float sq[8];
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-            ss = __builtin_fmaf(E::lo(lo[w]), E::lo(lo[w]), ss);
-            ss = __builtin_fmaf(E::hi(lo[w]), E::hi(lo[w]), ss);
-            ss = __builtin_fmaf(E::lo(hi[w]), E::lo(hi[w]), ss);
-            ss = __builtin_fmaf(E::hi(hi[w]), E::hi(hi[w]), ss);
+            sq[2 * w] = pair_sq(E::lo(lo[w]), E::lo(hi[w]));
+            sq[2 * w + 1] = pair_sq(E::hi(lo[w]), E::hi(hi[w]));
         }
-        ss += __shfl_xor(ss, 1);
-        ss += __shfl_xor(ss, 2);
+#pragma unroll
+        for (int b = 4; b >= 1; b >>= 1)
+#pragma unroll
+            for (int e = 0; e < b; ++e) {
+                const bool up = c & b;
+                const float keep = up ? sq[e + b] : sq[e], give = up ? sq[e] : sq[e + b];
+                sq[e] = keep + __shfl_xor(give, b);
+            }
+        float ss = sq[0];
         ss += __shfl_xor(ss, 4);
+        ss += __shfl_xor(ss, 2);
+        ss += __shfl_xor(ss, 1);
         const float inv = 1.0f / sqrtf(ss / (float)D + p.norm_eps);
         const u32x4 wl = *(const u32x4 *)(nw + 16 * c), wh = *(const u32x4 *)(nw + 16 * (c + 8));
 #pragma unroll

@@ -106,7 +106,7 @@ __global__ __launch_bounds__(NT) void qk_norm_rope_kernel(const QkParams p) {
         }
         return;
     }
-    float ss = x1 * x1 + x2 * x2;
+    float ss = pair_sq(x1, x2);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
     const float inv = 1.0f / sqrtf(ss / (float)D + p.eps);
