@@ -213,8 +213,11 @@ void attn_bf16_kernel(const AttnParams p) {
 template <int D, class E>
 hipError_t launch_d(const AttnParams &p, int mode, int grid, hipStream_t s) {
     switch (mode) {
-        case kModePrefill:   // D = 64 only
-            hipLaunchKernelGGL((attn_bf16_kernel<64, kModePrefill, E>), dim3(grid), dim3(THREADS), 0, s, p);
+        case kModePrefill:
+            if constexpr (D == 64)
+                hipLaunchKernelGGL((attn_bf16_kernel<D, kModePrefill, E>), dim3(grid), dim3(THREADS), 0, s, p);
+            else
+                return hipErrorInvalidValue;   // head_dim 128: the two-group kernels
             break;
         case kModeContinue:
             hipLaunchKernelGGL((attn_bf16_kernel<D, kModeContinue, E>), dim3(grid), dim3(THREADS), 0, s, p);
@@ -229,7 +232,6 @@ hipError_t launch_d(const AttnParams &p, int mode, int grid, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_attn_bf16(const AttnParams &p, int head_dim, int mode, bool f16, int grid, hipStream_t s) {
-    if (mode == kModePrefill && p.split_keys) return launch_attn_pk(p, head_dim, f16, grid, s);
     if (f16) return head_dim == 128 ? launch_d<128, F16>(p, mode, grid, s) : launch_d<64, F16>(p, mode, grid, s);
     return head_dim == 128 ? launch_d<128, Bf16>(p, mode, grid, s) : launch_d<64, Bf16>(p, mode, grid, s);
 }

@@ -558,7 +558,6 @@ __global__ __launch_bounds__(PP_THREADS) void attn_pp_kernel(const AttnParams p)
 }  // namespace
 
 hipError_t launch_attn_pp(const AttnParams &p, int mode, bool f16, int grid, hipStream_t s) {
-    if (mode == kModePrefill && p.split_keys) return launch_attn_pk(p, 128, f16, grid, s);
     if (mode == kModePrefill) {
         if (f16) hipLaunchKernelGGL((attn_pp_kernel<kModePrefill, F16>), dim3(grid), dim3(PP_THREADS), 0, s, p);
         else hipLaunchKernelGGL((attn_pp_kernel<kModePrefill, Bf16>), dim3(grid), dim3(PP_THREADS), 0, s, p);

@@ -469,10 +469,12 @@ int launch_single(const kvr_desc *d, int mode, const void *Q, const void *K, con
             e = launch_attn_cont(p, nct, qscale != nullptr, f16(d), (int)grid, stream);
         else
             e = launch_attn_rows(p, f16(d), (int)grid, stream);
+    } else if (mode == kModePrefill && is16(d) && use_pk(d, rows, n_tok)) {
+        const int64_t pk_tiles = (rows + kRowsPK - 1) / kRowsPK;
+        p.tiles_total = (int32_t)pk_tiles;
+        e = launch_attn_pk(p, d->head_dim, f16(d), (int)(pk_tiles * p.n_kv_heads), stream);
     } else if (mode == kModePrefill && use_pp(d)) {
-        p.split_keys = use_pk(d, rows, n_tok);
-        const int64_t rows_wg = p.split_keys ? kRowsPK : kRowsPP;
-        const int64_t pp_tiles = (rows + rows_wg - 1) / rows_wg;
+        const int64_t pp_tiles = (rows + kRowsPP - 1) / kRowsPP;
         p.tiles_total = (int32_t)pp_tiles;
         e = launch_attn_pp(p, kModePrefill, f16(d), (int)(pp_tiles * p.n_kv_heads), stream);
     } else if (mode == kModeContinue && use_pp_long(d, n_prefix, n_tok, sp)) {
@@ -484,7 +486,6 @@ int launch_single(const kvr_desc *d, int mode, const void *Q, const void *K, con
         e = launch_attn_pp(p, kModeContinue, f16(d),
                            (int)((lp.tail0 + (lp.tiles - lp.tail0) * lp.nsplit) * p.n_kv_heads), stream);
     } else if (is16(d)) {
-        p.split_keys = mode == kModePrefill && use_pk(d, rows, n_tok);
         e = launch_attn_bf16(p, d->head_dim, mode, f16(d), (int)grid, stream);
     } else {
         if (mode == kModePrefill && !keys_in_cache) {   // the fp32 kernel does not write the cache itself

@@ -66,7 +66,6 @@ struct AttnParams {
     float norm_eps;
     int64_t q_tok_stride;  // elements between tokens of q (keys-split kernel, with rope)
     int32_t row_tile;    // fp32 path: query rows per workgroup, 16 or 32
-    int32_t split_keys;  // 16-bit prefill: 1 runs the key-split kernel (row tiles of kRowsPK)
     int32_t stream_kv;   // keys-split kernel: 1 runs the instance that loads cached rows with the non-temporal hint
 };
 
@@ -107,8 +106,7 @@ hipError_t launch_merge_bf16(const MergeParams &p, int head_dim, bool f16, hipSt
 // matrix and softmax steps
 constexpr int kRowsPP = 256;   // query rows per workgroup (8 waves x 32)
 hipError_t launch_attn_pp(const AttnParams &p, int mode, bool f16, int grid, hipStream_t s);
-// 16-bit prefill with the keys split between the two groups (D in {64, 128});
-// launch_attn_pp (D = 128) and launch_attn_bf16 (D = 64) run it for split_keys
+// 16-bit prefill with the keys split between the two groups (D in {64, 128})
 constexpr int kRowsPK = 128;   // query rows per workgroup
 hipError_t launch_attn_pk(const AttnParams &p, int head_dim, bool f16, int grid, hipStream_t s);
 // bf16 continuation for G*S <= 96 rows (D = 128).  33..96 rows: the waves of

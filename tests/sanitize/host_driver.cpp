@@ -23,11 +23,31 @@ static int64_t g_pp_grid = -1, g_pp_tail0 = -1, g_pp_rows = -1;
 
 static int g_long = 0, g_long_bad = 0, g_long_split = 0;   // long continuations on the two-group kernel
 static size_t g_ws_given = (size_t)1 << 60;                // workspace bytes of the running call, where they are checked
-static char g_kernel = 0;                                  // the last attention launch: 's'taged, 'p' two-group, ...
+static char g_kernel = 0;                                  // the last attention launch: 's'taged, 'p' two-group, 'k'ey-split
+static int g_pre = 0, g_pre_bad = 0;                       // 16-bit prefills whose tiles were checked
 
 namespace kvr {
-hipError_t launch_attn_bf16(const AttnParams &, int, int mode, bool, int, hipStream_t) {
-    ++g_launches; if (mode == kModeContinue) g_kernel = 's'; return hipErrorUnknown;
+// a prefill's row tiles cover its rows, and the grid its tiles and kv heads
+static void check_prefill(const AttnParams &p, int64_t tile, int grid, char kernel) {
+    const int64_t rows = (int64_t)p.group * p.seg_tok0[1], tiles = (rows + tile - 1) / tile;
+    if (p.n_seg != 1 || p.seg_tok0[0] != 0 || p.tiles_total != tiles || (int64_t)grid != tiles * p.n_kv_heads) {
+        ++g_pre_bad;
+        fprintf(stderr, "prefill plan: kernel %c heads %d/%d rows %ld tiles %d grid %d\n", kernel, p.n_q_heads, p.n_kv_heads,
+                (long)rows, p.tiles_total, grid);
+    }
+    ++g_pre;
+    g_kernel = kernel;
+}
+hipError_t launch_attn_bf16(const AttnParams &p, int head_dim, int mode, bool, int grid, hipStream_t) {
+    ++g_launches;
+    if (mode == kModePrefill) {
+        check_prefill(p, kRowsBf16, grid, 's');
+        if (head_dim != 64) ++g_pre_bad;
+    } else if (mode == kModeContinue) g_kernel = 's';
+    return hipErrorUnknown;
+}
+hipError_t launch_attn_pk(const AttnParams &p, int, bool, int grid, hipStream_t) {
+    ++g_launches; check_prefill(p, kRowsPK, grid, 'k'); return hipErrorUnknown;
 }
 hipError_t launch_merge_bf16(const MergeParams &, int, bool, hipStream_t) { ++g_launches; return hipErrorUnknown; }
 // many readers on the two-group kernel: the packed plan must cover its tiles
@@ -58,6 +78,8 @@ hipError_t launch_attn_pp(const AttnParams &p, int mode, bool, int grid, hipStre
         ++g_long;
         g_long_split += ns > 1;
         g_kernel = 'p';
+    } else {
+        check_prefill(p, kRowsPP, grid, 'p');
     }
     return hipErrorUnknown;
 }
@@ -342,6 +364,28 @@ static void long_plans() {
     }
 }
 
+// 16-bit prefills over head counts and lengths: the tiles of the kernel they run on
+// (checked in the stubs).
+static void prefill_plans() {
+    void *P = (void *)(uintptr_t)0x100000;
+    const int heads[][2] = {{32, 8}, {8, 8}, {12, 3}, {64, 8}, {128, 8}, {512, 8}, {4, 1}, {16, 2}, {5, 5}, {96, 1}, {14, 2}};
+    const int64_t lens[] = {1, 2, 31, 33, 64, 65, 127, 129, 255, 257, 449, 513, 600, 945, 1200, 1473, 2047, 2049, 4097, 9000, 40000};
+    int seen[3] = {0, 0, 0};
+    for (const auto &h : heads)
+        for (int64_t L : lens)
+            for (int hd : {64, 128})
+                for (int dt : {KVR_BF16, KVR_F16}) {
+                    const kvr_desc d = desc(h[0], h[1], hd, dt, L);
+                    g_kernel = 0;
+                    EXPECT(kvr_prefill(&d, P, P, P, L, P, P, P, nullptr), KVR_ERR_DEVICE);
+                    if (g_kernel == (hd == 64 ? 's' : 'p')) ++seen[hd == 64];
+                    else if (g_kernel == 'k') ++seen[2];
+                    else { fprintf(stderr, "prefill %d/%d d=%d L=%ld: kernel %c\n", h[0], h[1], hd, (long)L, g_kernel); ++fails; }
+                }
+    if (g_pre_bad || g_pre < 900) { fprintf(stderr, "%d of %d prefills broke a plan invariant\n", g_pre_bad, g_pre); ++fails; }
+    if (seen[0] < 50 || seen[1] < 50 || seen[2] < 50) { fprintf(stderr, "prefill kernels seen: %d %d %d\n", seen[0], seen[1], seen[2]); ++fails; }
+}
+
 int main() {
     if (kvr_abi_version() != KVR_ABI_VERSION) {
         fprintf(stderr, "ABI version mismatch\n");
@@ -352,6 +396,7 @@ int main() {
     fixed_cases();
     split_plans();
     long_plans();
+    prefill_plans();
     fuzz();
     if (g_pp_bad) {
         fprintf(stderr, "%d many-readers launches broke a plan invariant\n", g_pp_bad);
