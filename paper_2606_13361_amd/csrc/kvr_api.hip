@@ -86,26 +86,37 @@ int rows_per_tile(const kvr_desc *d, int64_t rows) {
 
 // A 16-bit prefill takes at least its longest row tile, the one that sees every
 // key.  The key-split kernel (attn_pk.hip: tiles of 128 rows whose keys two
-// groups of waves share) halves that.
-//   head_dim 128, against 256-row tiles that every wave runs whole: pays while the
-//   256-row tiles leave compute units idle.  From 3/4 of them on, the second
-//   128-row workgroup of a compute unit costs its fixed time (query rows, first
-//   tiles, epilogue), about what 24 key tiles save.  Measured 256 -> 128 rows, 32 / 8
-//   heads: 255 tokens 14.9 -> 12.3 us, 945 30.8 -> 23.3, 1300 38.4 -> 28.5, 1900 (240
-//   workgroups of 256 rows, 30 key tiles) 51.5 -> 46.2; 64 / 8 heads, 900 (232, 15
-//   key tiles) 35.6 -> 36.8; beyond: 2800 (352) 78.7 -> 89.3.
+// groups of waves share) halves that, for a fixed time of its own: the two groups'
+// merge, and a second workgroup on a compute unit.
+//   head_dim 128, against 256-row tiles that every wave runs whole.  One round of
+//   128-row workgroups pays once there is anything to split, more than one tile of
+//   rows or of keys (256 -> 128 rows, 32 / 8 heads: 255 tokens 14.9 -> 12.3 us, 945
+//   30.8 -> 23.3, 50 8.7 -> 8.1; a single tile: 20 tokens 7.3 -> 7.5, of 16 / 16 heads
+//   5.5 -> 6.5, 64 7.5 -> 7.7).  Two rounds save half the key tiles and cost a
+//   workgroup's fixed time, and the more 256-row workgroups there would be, the
+//   fewer units idle: up to 160 of them it pays from 6 key tiles on (96 / 8 heads, 343
+//   tokens 18.0 -> 16.7, 423 19.9 -> 19.8; below: 128 / 8 heads, 317 17.1 -> 18.2, 512 / 8
+//   heads, 77 12.2 -> 16.4), up to 191 from 9 on (32 / 8 heads, 1501 42.4 -> 35.0, 64 / 8
+//   heads, 701 25.6 -> 23.8; below: 96 / 8 heads, 466 21.3 -> 22.1, 256 / 8 heads, 173
+//   13.9 -> 17.8), and up to 255 from 23 on (32 / 8 heads, 1900 51.5 -> 46.2; below:
+//   64 / 8 heads, 900 35.6 -> 36.8).  Beyond: 2800 tokens (352) 78.7 -> 89.3.
 //   head_dim 64, against the register-staged 128-row tiles (two workgroups per
-//   compute unit): pays in one round of workgroups, and in two where the longest
-//   tile is long.  16 / 2 heads, 2047 tokens 42.8 -> 29.3 us, 4000 (500 workgroups)
-//   82.7 -> 58.9, 32 / 8 heads 2000 (504) 44.7 -> 38.4; 64 / 8 heads 1000 (500, 16 key
-//   tiles) 25.1 -> 26.1; beyond: 16 / 2 heads 8000 (1000) 179 -> 191.
+//   compute unit): pays in one round of workgroups from 8 key tiles on, and in two
+//   where the longest tile is long.  16 / 2 heads, 600 tokens 14.7 -> 13.7 us, 2047 42.8
+//   -> 29.3, 4000 (500 workgroups) 82.7 -> 58.9, 32 / 8 heads 2000 (504) 44.7 -> 38.4;
+//   even at 400 to 500 tokens; below: 32 / 8 heads, 29 tokens 4.8 -> 6.0, 321 9.6 -> 10.5;
+//   64 / 8 heads, 1000 (500, 16 key tiles) 25.1 -> 26.1; beyond: 16 / 2 heads 8000 (1000)
+//   179 -> 191.
 constexpr int64_t kPkLongTokens = 23 * kKeyTile;
 bool use_pk(const kvr_desc *d, int64_t rows, int64_t n_tok) {
     const int64_t tile = d->head_dim == 64 ? kRowsPK : kRowsPP;
     const int64_t wgs = (rows + tile - 1) / tile * d->n_kv_heads;
-    const int64_t any = d->head_dim == 64 ? kCus : kCus * 3 / 4 - 1;
-    const int64_t most = d->head_dim == 64 ? 2 * kCus : kCus - 1;
-    return wgs <= any || (wgs <= most && n_tok > kPkLongTokens);
+    if (d->head_dim == 64)
+        return n_tok > 8 * kKeyTile && (wgs <= kCus || (wgs <= 2 * kCus && n_tok > kPkLongTokens));
+    if ((rows + kRowsPK - 1) / kRowsPK * d->n_kv_heads <= kCus) return rows > kRowsPK || n_tok > kKeyTile;
+    if (wgs <= kCus * 5 / 8) return n_tok > 6 * kKeyTile;
+    if (wgs < kCus * 3 / 4) return n_tok > 9 * kKeyTile;
+    return wgs < kCus && n_tok > kPkLongTokens;
 }
 
 struct Split {

@@ -365,7 +365,7 @@ static void long_plans() {
 }
 
 // 16-bit prefills over head counts and lengths: the tiles of the kernel they run on
-// (checked in the stubs).
+// (checked in the stubs), and the route of calls that measured faster on one kernel.
 static void prefill_plans() {
     void *P = (void *)(uintptr_t)0x100000;
     const int heads[][2] = {{32, 8}, {8, 8}, {12, 3}, {64, 8}, {128, 8}, {512, 8}, {4, 1}, {16, 2}, {5, 5}, {96, 1}, {14, 2}};
@@ -382,6 +382,41 @@ static void prefill_plans() {
                     else if (g_kernel == 'k') ++seen[2];
                     else { fprintf(stderr, "prefill %d/%d d=%d L=%ld: kernel %c\n", h[0], h[1], hd, (long)L, g_kernel); ++fails; }
                 }
+    struct Route { int hq, hkv, hd; int64_t L; char want; };
+    const Route routes[] = {
+        // us whole tiles, key-split
+        {32, 8, 64, 29, 's'},       // 4.8, 6.0
+        {32, 32, 64, 157, 's'},     // 7.0, 7.9
+        {128, 8, 64, 247, 's'},     // 8.8, 9.8
+        {64, 8, 64, 321, 's'},      // 9.8, 10.3
+        {16, 2, 64, 600, 'k'},      // 14.7, 13.7
+        {16, 2, 64, 2047, 'k'},     // 42.8, 29.3
+        {64, 8, 64, 1000, 's'},     // 25.1, 26.1
+        {32, 8, 128, 1, 'p'},       // 5.0, 6.1
+        {16, 16, 128, 20, 'p'},     // 5.5, 6.5
+        {1024, 64, 128, 7, 'p'},    // 7.8, 8.1
+        {32, 8, 128, 50, 'k'},      // 8.7, 8.1
+        {16, 16, 128, 125, 'k'},    // 11.5, 10.9
+        {128, 8, 128, 317, 'p'},    // 17.1, 18.2
+        {512, 8, 128, 77, 'p'},     // 12.2, 16.4
+        {256, 8, 128, 173, 'p'},    // 13.9, 17.8
+        {96, 8, 128, 466, 'p'},     // 21.3, 22.1
+        {128, 8, 128, 251, 'k'},    // 15.1, 13.4
+        {80, 8, 128, 457, 'k'},     // 21.0, 18.4
+        {64, 8, 128, 701, 'k'},     // 25.6, 23.8
+        {32, 8, 128, 945, 'k'},     // 30.8, 23.3
+        {32, 8, 128, 1797, 'k'},    // 49.9, 44.4
+        {64, 8, 128, 900, 'p'},     // 35.6, 36.8
+    };
+    for (const Route &r : routes) {
+        const kvr_desc d = desc(r.hq, r.hkv, r.hd, KVR_BF16, r.L);
+        g_kernel = 0;
+        EXPECT(kvr_prefill(&d, P, P, P, r.L, P, P, P, nullptr), KVR_ERR_DEVICE);
+        if (g_kernel != r.want) {
+            fprintf(stderr, "prefill %d/%d d=%d L=%ld: kernel %c, want %c\n", r.hq, r.hkv, r.hd, (long)r.L, g_kernel, r.want);
+            ++fails;
+        }
+    }
     if (g_pre_bad || g_pre < 900) { fprintf(stderr, "%d of %d prefills broke a plan invariant\n", g_pre_bad, g_pre); ++fails; }
     if (seen[0] < 50 || seen[1] < 50 || seen[2] < 50) { fprintf(stderr, "prefill kernels seen: %d %d %d\n", seen[0], seen[1], seen[2]); ++fails; }
 }
