@@ -68,6 +68,17 @@ static_assert(merge_bytes<3>() <= LDS_BYTES, "merge buffers exceed the LDS alloc
 __device__ __forceinline__ int swz(int row) { return ((row >> 2) & 3) | ((row & 3) << 2); }
 
 
+// The value of the lane B (1, 2 or 4) apart in a row's eight, by data-parallel moves
+template <int B>
+__device__ __forceinline__ float lane_xor(float x) {
+    int v = (int)__float_as_uint(x);
+    if constexpr (B == 1) v = __builtin_amdgcn_mov_dpp(v, 0xB1, 0xf, 0xf, true);        // quad_perm 1, 0, 3, 2
+    else if constexpr (B == 2) v = __builtin_amdgcn_mov_dpp(v, 0x4E, 0xf, 0xf, true);   // quad_perm 2, 3, 0, 1
+    else v = __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(v, 0x141, 0xf, 0xf, true),   // half row mirrored,
+                                      0x1B, 0xf, 0xf, true);                            // then quad_perm 3, 2, 1, 0
+    return __uint_as_float((uint32_t)v);
+}
+
 // Rotation in the kernel, in LDS: eight lanes a row, lane c of them dims 8c ..
 // 8c + 7 and their partners 64 further (the norm's sum of squares meets in the
 // eight), the same operations, rounding and order of sums as the pre-pass of either
@@ -82,10 +93,8 @@ __device__ __forceinline__ void rotate_row(const AttnParams &p, unsigned char *r
     hi = *ph;
     const float *cs = (const float *)(fuse_lds + tk * CSB) + 16 * c;
     if (p.q_norm) {
-        // pair 8c + e sits in lane c, element e.  Distances 32, 16, 8 are those of lanes
-        // 4, 2, 1 apart, each step leaving a lane the half of its elements whose index
-        // bit equals its own; lane c then holds the sum of elements e = c, and
-        // distances 4, 2, 1 are lanes once more.
+        // pair 8c + e sits in lane c, element e: distances 32, 16 and 8 are those of lanes
+        // 4, 2 and 1 apart, distances 4, 2 and 1 those of the elements
         float sq[8];
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
@@ -93,17 +102,12 @@ __device__ __forceinline__ void rotate_row(const AttnParams &p, unsigned char *r
             sq[2 * w + 1] = pair_sq(E::hi(lo[w]), E::hi(hi[w]));
         }
 #pragma unroll
-        for (int b = 4; b >= 1; b >>= 1)
-#pragma unroll
-            for (int e = 0; e < b; ++e) {
-                const bool up = c & b;
-                const float keep = up ? sq[e + b] : sq[e], give = up ? sq[e] : sq[e + b];
-                sq[e] = keep + __shfl_xor(give, b);
-            }
-        float ss = sq[0];
-        ss += __shfl_xor(ss, 4);
-        ss += __shfl_xor(ss, 2);
-        ss += __shfl_xor(ss, 1);
+        for (int e = 0; e < 8; ++e) {
+            sq[e] += lane_xor<4>(sq[e]);
+            sq[e] += lane_xor<2>(sq[e]);
+            sq[e] += lane_xor<1>(sq[e]);
+        }
+        const float ss = ((sq[0] + sq[4]) + (sq[2] + sq[6])) + ((sq[1] + sq[5]) + (sq[3] + sq[7]));
         const float inv = 1.0f / sqrtf(ss / (float)D + p.norm_eps);
         const u32x4 wl = *(const u32x4 *)(nw + 16 * c), wh = *(const u32x4 *)(nw + 16 * (c + 8));
 #pragma unroll
