@@ -260,14 +260,19 @@ ReaderPlan plan_long(const kvr_desc *d, int64_t L_prefix, int64_t S, size_t ws_b
 // several passes.  (The constants are a least-squares fit to both kernels' times at
 // 2596 sizes: 12 head counts from 4 / 1 to 32 / 32, 97 to 6000 rows over 130 to 32000 keys; it
 // misses by 7 % rms.)
-// Measured by this rule, 70 of the sizes end more than 2 % behind the staged kernel,
-// the worst 11 %; the mean of all is 0.5 % behind the faster of the two.  Staged ->
-// two-group where it picks the second, 32 / 8 heads: 517 tokens over 7001 129.8 -> 87.5
+// The two-group kernel is taken where it is expected to be 2 % faster, and a tenth where
+// the fit overrates the staged kernel: against fewer than 3/2 staged workgroups per
+// compute unit (unless the two-group plan needs no merge), and with more than 24 splits.
+// Of 2041 other sizes (13 head counts, 16 to 2048 tokens over 128 to 32768) it then runs
+// 740, two of them behind the staged kernel (by 1.4 and 5.6 %), and the mean of all is 0.906
+// of the staged times; without the tenth it runs 766, twelve behind by up to 15 %, and the
+// mean is the same.
+// Staged -> two-group where it picks the second, 32 / 8 heads: 517 tokens over 7001 129.8 -> 87.5
 // us, 300 over 20000 188 -> 115, 500 over 2000 51.3 -> 44.7, 1024 over 1000 74 -> 60.5;
 // where it stays: 100 over 4000 25.6 (28.2), 300 over 1000 33.7 (33.5), 4 / 1 heads: 512
 // over 300 24.9 (31.1), 64 over 16000 24.2 (28.9).
 // A prefix of fewer than four key tiles leaves nothing to split: staged.
-constexpr double kPreferStaged = 1.02;   // the fit's tie: what ran there before
+constexpr double kPreferStaged = 1.02, kPreferStagedFar = 1.10;
 bool use_pp_long(const kvr_desc *d, int64_t L_prefix, int64_t S, const Split &sp) {
     const int64_t G = d->n_q_heads / d->n_kv_heads;
     const int64_t rows = G * S, keys = L_prefix + S;
@@ -304,7 +309,8 @@ bool use_pp_long(const kvr_desc *d, int64_t L_prefix, int64_t S, const Split &sp
     const Wait lw = wait(lp.tiles * d->n_kv_heads * lp.nsplit, kCus, lp.nsplit);
     const int64_t l_chain = (key_tiles + lp.nsplit - 1) / lp.nsplit;
     const double two_group = 9.3 + 8.0 * lw.rounds + 1.7 * ((double)l_chain + lw.tiles) + merge_us(lp.nsplit, 3.5, 1.5);
-    return two_group * kPreferStaged < staged;
+    const bool overrated = (lp.nsplit > 1 && 2 * sw <= 3 * kCus) || lp.nsplit > 24;
+    return two_group * (overrated ? kPreferStagedFar : kPreferStaged) < staged;
 }
 
 int to_status(hipError_t e) { return e == hipSuccess ? KVR_OK : KVR_ERR_DEVICE; }

@@ -345,6 +345,12 @@ static void long_plans() {
         {32, 8, 1000, 1024, 'p'},   // 74.2, 60.5
         {8, 8, 4000, 768, 'p'},     // 58.5, 38.3
         {4, 1, 20000, 1500, 'p'},   // 150.9, 80.2
+        {4, 1, 8297, 161, 's'},     // 21.8, 25.0
+        {8, 8, 953, 517, 's'},      // 28.8, 31.3
+        {12, 3, 1643, 385, 's'},    // 29.7, 31.8
+        {16, 2, 8789, 111, 's'},    // 28.4, 30.6
+        {4, 1, 32763, 122, 's'},    // 32.3, 33.7
+        {32, 8, 459, 660, 'p'},     // 48.2, 39.0
     };
     for (const Route &r : routes) {
         const kvr_desc d = desc(r.hq, r.hkv, 128, KVR_BF16, 40000);
