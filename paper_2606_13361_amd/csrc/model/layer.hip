@@ -154,13 +154,12 @@ __global__ __launch_bounds__(NT) void silu_mul_kernel(const uint16_t *gu, uint16
 // built once per workgroup in LDS by the prologue:
 //   kPlain  x' = x
 //   kNorm   x' = round(rmsnorm(x) * ln)           (the layer's input norms)
-//   kSilu   x' = round(silu(x[k]) * x[K + k])     (x = the gate|up row)
-// so the norm and the activation need no launch of their own.
-enum { kPlain = 0, kNorm = 1, kSilu = 2 };
+// so the norm needs no launch of its own.
+enum { kPlain = 0, kNorm = 1 };
 constexpr int kGemvMaxK = 16384;
 
 struct GemvParams {
-    const uint16_t *x;     // [K] (kSilu: [2K])
+    const uint16_t *x;     // [K]
     const uint16_t *w;     // [N][K]
     const uint16_t *ln;    // [K] (kNorm)
     uint16_t *y;           // [N]
@@ -206,18 +205,6 @@ __device__ __forceinline__ void build_x(const GemvParams &p, uint16_t *xs, float
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 o[i] = E::pack2(E::lo(v[i]) * inv * E::lo(g[i]), E::hi(v[i]) * inv * E::hi(g[i]));
-            *(u32x4 *)(xs + 8 * c) = o;
-        }
-    } else if (PRO == kSilu) {
-        for (int c = tid; c < KC; c += NTH) {
-            const u32x4 g = *(const u32x4 *)(p.x + 8 * c);
-            const u32x4 u = *(const u32x4 *)(p.x + p.K + 8 * c);
-            u32x4 o;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float g0 = E::lo(g[i]), g1 = E::hi(g[i]);
-                o[i] = E::pack2(silu(g0) * E::lo(u[i]), silu(g1) * E::hi(u[i]));
-            }
             *(u32x4 *)(xs + 8 * c) = o;
         }
     } else {
@@ -444,8 +431,7 @@ int gemv(int32_t dtype, int pro, const void *x, const void *ln, float eps, const
                                    else if (nwv == 16) KVR_GEMV1_W(E_, P_, U_, 16); else KVR_GEMV1_W(E_, P_, U_, 8); } while (0)
 #define KVR_GEMV1_U(E_, P_) do { if (steps <= 5) KVR_GEMV1(E_, P_, 5); else if (steps <= 8) KVR_GEMV1(E_, P_, 8); \
                                  else KVR_GEMV1(E_, P_, kGemv1MaxSteps); } while (0)
-#define KVR_GEMV1_PRO(E_) do { if (pro == kNorm) KVR_GEMV1_U(E_, kNorm); else if (pro == kSilu) KVR_GEMV1_U(E_, kSilu); \
-                               else KVR_GEMV1_U(E_, kPlain); } while (0)
+#define KVR_GEMV1_PRO(E_) do { if (pro == kNorm) KVR_GEMV1_U(E_, kNorm); else KVR_GEMV1_U(E_, kPlain); } while (0)
         if (dtype == KVR_F16) KVR_GEMV1_PRO(F16);
         else KVR_GEMV1_PRO(Bf16);
 #undef KVR_GEMV1_PRO
@@ -460,8 +446,7 @@ int gemv(int32_t dtype, int pro, const void *x, const void *ln, float eps, const
 #define KVR_GEMV(E_, P_, R_, U_) hipLaunchKernelGGL((gemv_kernel<E_, P_, R_, 0, U_>), grid, dim3(GT), 0, s, g)
 #define KVR_GEMV_RW(E_, P_) do { if (rw == 1) KVR_GEMV(E_, P_, 1, 8); else if (two_row_steps(steps) == 5) KVR_GEMV(E_, P_, 2, 5); \
                                  else KVR_GEMV(E_, P_, 2, 4); } while (0)
-#define KVR_GEMV_PRO(E_) do { if (pro == kNorm) KVR_GEMV_RW(E_, kNorm); else if (pro == kSilu) KVR_GEMV_RW(E_, kSilu); \
-                              else KVR_GEMV_RW(E_, kPlain); } while (0)
+#define KVR_GEMV_PRO(E_) do { if (pro == kNorm) KVR_GEMV_RW(E_, kNorm); else KVR_GEMV_RW(E_, kPlain); } while (0)
     if (dtype == KVR_F16) KVR_GEMV_PRO(F16);
     else KVR_GEMV_PRO(Bf16);
 #undef KVR_GEMV_PRO
