@@ -169,6 +169,15 @@ struct GemvParams {
     float eps;
 };
 
+// Bytes of a weight matrix from which on it is loaded as a stream (see gemv_kernel): the
+// largest matrix of a layer stays below up to hidden 700 or so, 10 MB a layer
+constexpr int64_t kStreamBytes = 6 << 20;
+template <bool NT>
+__device__ __forceinline__ u32x4 load_weights(const u32x4 *w) {
+    if constexpr (NT) return __builtin_nontemporal_load(w);
+    else return *w;
+}
+
 constexpr int GT = 512;            // threads of a one-row-product workgroup
 constexpr int kGemvMaxGrid = 512;  // workgroups: two per compute unit
 
@@ -223,10 +232,15 @@ __device__ __forceinline__ void build_x(const GemvParams &p, uint16_t *xs, float
 // gate and up product of 99.6 MB took 20.5 us in a one-token step, this way 16.7 to
 // 17.5; three workgroups per compute unit, or one, cost the 12-layer step 2 %, ten waves
 // per workgroup as well.
-// The weights are loaded with the non-temporal hint, here and in gemv1_kernel: a step
-// reads each once, and the model's next step comes after more bytes than any cache
-// holds (12-layer step 820 -> 790 us, one layer by itself 58.0 -> 55.0).
-template <class E, int PRO, int RW, int PAIR, int U>
+// NT: the weights are loaded with the non-temporal hint, here and in gemv1_kernel: a step
+// reads each once, and the model's next step comes after more bytes than the last-level
+// cache (256 MB) holds (12-layer step 820 -> 790 us, one layer by itself 58.0 -> 55.0).
+// Weights that stay in that cache come slower with it (4096 x 1000, 24 matrices in turn
+// 4.3 -> 4.7 us), so matrices below kStreamBytes, whose whole model fits, are loaded without
+// (24 layers of hidden 512, inter 2048, 8 / 8 heads of 64, over 700 tokens 28.5 -> 26.5 us a
+// layer; hidden 1024 and 1536 take 27.2 and 37.6 us, 25.7 and 36.3 if all were streamed and
+// 27.4 and 38.7 if none).
+template <class E, int PRO, int RW, int PAIR, int U, bool NT>
 __global__ __launch_bounds__(GT) void gemv_kernel(const GemvParams p) {
     static_assert(!PAIR || RW == 2, "a pair is two rows");
     __shared__ __attribute__((aligned(16))) uint16_t xs[kGemvMaxK];
@@ -251,7 +265,7 @@ __global__ __launch_bounds__(GT) void gemv_kernel(const GemvParams p) {
         for (int r = 0; r < RW; ++r) {
             const int64_t row = PAIR ? (nb < p.N ? nb : p.N - 1) + r * p.N
                                      : (nb + r < p.N ? nb + r : p.N - 1);
-            wv[u][r] = __builtin_nontemporal_load((const u32x4 *)((const char *)(p.w + row * p.K) + at));
+            wv[u][r] = load_weights<NT>((const u32x4 *)((const char *)(p.w + row * p.K) + at));
         }
     };
     // the first weights do not depend on x: in flight while the prologue runs
@@ -317,7 +331,7 @@ constexpr int64_t kGemv1MaxRows = 8192;
 constexpr int64_t kGemv1Cus = 256;    // compute units of the part (MI355X)
 constexpr int kGemv1MaxSteps = 19;   // K = 9728 (the Qwen3-4B MLP width) exactly
 
-template <class E, int PRO, int U, int NWV>
+template <class E, int PRO, int U, int NWV, bool NT>
 __global__ __launch_bounds__(64 * NWV) void gemv1_kernel(const GemvParams p) {
     constexpr int NTH = 64 * NWV;
     __shared__ __attribute__((aligned(16))) uint16_t xs[kGemvMaxK];
@@ -342,7 +356,7 @@ __global__ __launch_bounds__(64 * NWV) void gemv1_kernel(const GemvParams p) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         const int c = min(lane + 64 * u, KC - 1);    // past K: loaded, never used
-        wv[u] = __builtin_nontemporal_load((const u32x4 *)(p.w + row * p.K + 8 * c));
+        wv[u] = load_weights<NT>((const u32x4 *)(p.w + row * p.K + 8 * c));
     }
     if constexpr (PRO == kPlain) {
 #pragma unroll
@@ -414,6 +428,7 @@ int gemv(int32_t dtype, int pro, const void *x, const void *ln, float eps, const
     g.beta = beta;
     g.eps = eps;
     const int steps = (K / 8 + 63) / 64;
+    const bool nt = 2 * N * K >= kStreamBytes;
     if (N <= kGemv1MaxRows && steps <= kGemv1MaxSteps) {
         // waves per workgroup: the fewest rows on the busiest CU (kGemv1Cus
         // compute units, one workgroup each per round), ties to the larger
@@ -426,7 +441,8 @@ int gemv(int32_t dtype, int pro, const void *x, const void *ln, float eps, const
             if (best < 0 || busiest <= best) { best = busiest; nwv = c; }
         }
         const dim3 grid1((unsigned)((N + nwv - 1) / nwv));
-#define KVR_GEMV1_W(E_, P_, U_, W_) hipLaunchKernelGGL((gemv1_kernel<E_, P_, U_, W_>), grid1, dim3(64 * W_), 0, s, g)
+#define KVR_GEMV1_W(E_, P_, U_, W_) do { if (nt) hipLaunchKernelGGL((gemv1_kernel<E_, P_, U_, W_, true>), grid1, dim3(64 * W_), 0, s, g); \
+                                         else hipLaunchKernelGGL((gemv1_kernel<E_, P_, U_, W_, false>), grid1, dim3(64 * W_), 0, s, g); } while (0)
 #define KVR_GEMV1(E_, P_, U_) do { if (nwv == 10) KVR_GEMV1_W(E_, P_, U_, 10); else if (nwv == 12) KVR_GEMV1_W(E_, P_, U_, 12); \
                                    else if (nwv == 16) KVR_GEMV1_W(E_, P_, U_, 16); else KVR_GEMV1_W(E_, P_, U_, 8); } while (0)
 #define KVR_GEMV1_U(E_, P_) do { if (steps <= 5) KVR_GEMV1(E_, P_, 5); else if (steps <= 8) KVR_GEMV1(E_, P_, 8); \
@@ -443,7 +459,8 @@ int gemv(int32_t dtype, int pro, const void *x, const void *ln, float eps, const
     const int rw = N >= 65536 ? 2 : 1;
     const int64_t groups = (N + rw * (GT / 64) - 1) / (rw * (GT / 64));
     const dim3 grid((unsigned)(groups < kGemvMaxGrid ? groups : kGemvMaxGrid));
-#define KVR_GEMV(E_, P_, R_, U_) hipLaunchKernelGGL((gemv_kernel<E_, P_, R_, 0, U_>), grid, dim3(GT), 0, s, g)
+#define KVR_GEMV(E_, P_, R_, U_) do { if (nt) hipLaunchKernelGGL((gemv_kernel<E_, P_, R_, 0, U_, true>), grid, dim3(GT), 0, s, g); \
+                                      else hipLaunchKernelGGL((gemv_kernel<E_, P_, R_, 0, U_, false>), grid, dim3(GT), 0, s, g); } while (0)
 #define KVR_GEMV_RW(E_, P_) do { if (rw == 1) KVR_GEMV(E_, P_, 1, 8); else if (two_row_steps(steps) == 5) KVR_GEMV(E_, P_, 2, 5); \
                                  else KVR_GEMV(E_, P_, 2, 4); } while (0)
 #define KVR_GEMV_PRO(E_) do { if (pro == kNorm) KVR_GEMV_RW(E_, kNorm); else KVR_GEMV_RW(E_, kPlain); } while (0)
@@ -470,7 +487,9 @@ int gemv_gate_up(int32_t dtype, const void *x, const void *ln, float eps, const 
     g.eps = eps;
     const int64_t groups = (I + GT / 64 - 1) / (GT / 64);
     const dim3 grid((unsigned)(groups < kGemvMaxGrid ? groups : kGemvMaxGrid));
-#define KVR_PAIR(E_, U_) hipLaunchKernelGGL((gemv_kernel<E_, kNorm, 2, 1, U_>), grid, dim3(GT), 0, s, g)
+    const bool nt = 4 * I * K >= kStreamBytes;
+#define KVR_PAIR(E_, U_) do { if (nt) hipLaunchKernelGGL((gemv_kernel<E_, kNorm, 2, 1, U_, true>), grid, dim3(GT), 0, s, g); \
+                              else hipLaunchKernelGGL((gemv_kernel<E_, kNorm, 2, 1, U_, false>), grid, dim3(GT), 0, s, g); } while (0)
     const bool five = two_row_steps((K / 8 + 63) / 64) == 5;
     if (dtype == KVR_F16) { if (five) KVR_PAIR(F16, 5); else KVR_PAIR(F16, 4); }
     else { if (five) KVR_PAIR(Bf16, 5); else KVR_PAIR(Bf16, 4); }
@@ -610,8 +629,8 @@ int kvr_layer_forward(const kvr_desc *desc, const kvr_layer_shape *shape, const 
     const int Wq = (Hq + 2 * Hkv) * D;
     void *blws = b + lw.blas;
 
-    // one token: the one-row products with the norms and the activation in
-    // their prologues; more tokens: separate norm / activation kernels and
+    // one token: the one-row products with the norms in their prologues and the
+    // activation in an epilogue; many tokens: separate norm / activation kernels and
     // hipBLASLt products
     const bool one = T == 1 && H <= kGemvMaxK && I <= kGemvMaxK && Hq * D <= kGemvMaxK;
 

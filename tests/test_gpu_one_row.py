@@ -1,6 +1,7 @@
 """One-row products (a decode step's linear layers): contraction lengths on both
 sides of a 512-element step and of blocks of four, five and eight steps, output
-counts that leave a last pair or round of waves ragged.  kvr_linear against fp64
+counts that leave a last pair or round of waves ragged, weights on both sides of the
+size from which they are loaded as a stream.  kvr_linear against fp64
 within half a bf16 step (8 significant bits: at most 2^-8 |y|) plus K roundings of the
 fp32 sum (K 2^-24 sum |x w|); the gate/up product, which pairs its rows, through a
 one-token layer at the layer tests' bars (|d| <= 2^-6 |x| + 2e-2, normalized rms 2^-7)."""
@@ -19,7 +20,8 @@ BF16 = torch.bfloat16
 
 
 @pytest.mark.parametrize("K,N", [(2560, 65536), (2568, 65544), (4104, 65552), (512, 65560), (2560, 8200), (4096, 12296),
-                                 (9736, 40), (16384, 8)])
+                                 (9736, 40), (16384, 8), (2560, 1000), (4096, 760), (4096, 768), (9728, 320),
+                                 (9728, 328), (128, 9000)])
 def test_one_row_linear(K, N):
     print("one row: K %d N %d" % (K, N), flush=True)
     g = torch.Generator(device=DEV)
