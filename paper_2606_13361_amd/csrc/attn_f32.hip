@@ -1,7 +1,7 @@
 // attn_f32.hip -- the fp32 member of the attention family: the same rows,
 // segments and causal offset as the 16-bit kernels, computed entirely in fp32
-// (fp32 matrix instructions, no reduced precision anywhere), for inputs whose
-// tolerance is 1e-5.
+// (fp32 matrix instructions; the hardware's 2^x, within an ulp, for the weights), for
+// inputs whose tolerance is 1e-5.
 //
 // What bounds it: the fp32 matrix rate, 256 flops per clock and CU.  A
 // workgroup is 8 waves (two per SIMD) that all hold the same 16 * NCT query
@@ -26,10 +26,11 @@
 //
 // Measured against the vector-ALU kernel this one replaces (64 rows per
 // workgroup, the keys one after another), 32 / 8 heads, d = 128: 24 tokens over
-// 945 cached rows 438 -> 27.7 us (48 workgroups: the bound is their own 14 us of
-// matrix time), prefill 1000 491 -> 112 us, 4000 4257 -> 1274 us (103 TFLOP/s of
-// the 157 peak); one token over 700 rows 372 -> 24 us.  Error against 64 bits at
-// the first shape: 7.4e-7 -> 3.3e-7 (2-norm).
+// 945 cached rows 438 -> 28 us (48 workgroups: the bound is their own 14 us of
+// matrix time), prefill 1000 491 -> 114 us, 4000 4257 -> 1274 us (103 TFLOP/s of
+// the 157 peak); one token over 700 rows 372 -> 24 us.  Error against 64 bits
+// (2-norm) at the first shape 7.4e-7 -> 2.8e-7; with 16 times larger scores 8.9e-7 ->
+// 8.2e-7 (1.24e-6 with scores of two chains).
 #include <type_traits>
 
 #include "attn_common.hpp"
@@ -63,6 +64,10 @@ __device__ __forceinline__ float row_sum(float x) {
     const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return dev::pair_sum(__uint_as_float(a[0]) + __uint_as_float(a[1]));
 }
+
+// e^t for t <= 0.  (t log2(e) is rounded: that moves a weight by |t| 2^-24 of itself, at
+// most 2e-8 of the row's largest.)
+__device__ __forceinline__ float exp_neg(float t) { return __builtin_amdgcn_exp2f(t * 1.44269504f); }
 
 template <int D, int NCT>
 __global__ __launch_bounds__(THREADS) void attn_f32_kernel(const AttnParams p) {
@@ -132,8 +137,7 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(const AttnParams p) {
         }
     }
 
-    // log2 domain: 2^(s - m) with s the product times scale * log2(e)
-    const float c2 = p.scale_log2;
+    const float scale = p.scale;
     const float *kc = (const float *)p.kc + (int64_t)g * p.cap * D;
     const float *vc = (const float *)p.vc + (int64_t)g * p.cap * D;
     const int64_t nstride = p.new_tok_stride;
@@ -162,23 +166,28 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(const AttnParams p) {
     auto stage = [&](int t, auto more_tag) {
         constexpr bool more = decltype(more_tag)::value;
         const int64_t key0 = (int64_t)t * SK;
-        f32x4 s0[NCT], s1[NCT];
-#pragma unroll
-        for (int c = 0; c < NCT; ++c) s0[c] = s1[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
         if constexpr (more) point(t + NW);
+        // a score is four chains of D / 4 products, added in pairs: in two chains the
+        // longer sums put the outputs of peaked rows up to 1.6 times further off
+        float w[NCT][4];
 #pragma unroll
-        for (int i = 0; i < NC; ++i) {
+        for (int c = 0; c < NCT; ++c) {
+            f32x4 s[4];
 #pragma unroll
-            for (int c = 0; c < NCT; ++c) {
-                s0[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][0], q[c][i][0], s0[c], 0, 0, 0);
-                s1[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][1], q[c][i][1], s1[c], 0, 0, 0);
-                s0[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][2], q[c][i][2], s0[c], 0, 0, 0);
-                s1[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][3], q[c][i][3], s1[c], 0, 0, 0);
+            for (int e = 0; e < 4; ++e) s[e] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < NC; ++i) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    s[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][e], q[c][i][e], s[e], 0, 0, 0);
+                if constexpr (more) {
+                    if (c == NCT - 1) kload(i);
+                }
             }
-            if constexpr (more) kload(i);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[c][e] = (s[0][e] + s[1][e]) + (s[2][e] + s[3][e]);
         }
         const bool masked = key0 + SK > k_full;
-        float w[NCT][4];
 #pragma unroll
         for (int c = 0; c < NCT; ++c) {
 #pragma clang fp contract(off)
@@ -187,18 +196,18 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(const AttnParams p) {
             float mx = -INFINITY;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float s = (s0[c][e] + s1[c][e]) * c2;
-                w[c][e] = masked && key0 + 4 * kg + e > pos[c] ? -INFINITY : s;
+                const float x = w[c][e] * scale;
+                w[c][e] = masked && key0 + 4 * kg + e > pos[c] ? -INFINITY : x;
                 mx = fmaxf(mx, w[c][e]);
             }
             const float m_new = fmaxf(m_run[c], row_max(mx));
             const float m_use = m_new == -INFINITY ? 0.f : m_new;   // nothing visible so far
-            const float alpha = __builtin_amdgcn_exp2f(m_run[c] - m_use);
+            const float alpha = exp_neg(m_run[c] - m_use);
             m_run[c] = m_new;
             float sum = 0.f;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                w[c][e] = __builtin_amdgcn_exp2f(w[c][e] - m_use);
+                w[c][e] = exp_neg(w[c][e] - m_use);
                 sum += w[c][e];
             }
             if (__ballot(alpha != 1.f)) {
@@ -273,7 +282,7 @@ __global__ __launch_bounds__(THREADS) void attn_f32_kernel(const AttnParams p) {
 #pragma unroll
         for (int x = 0; x < NW; ++x) {
             const float mx = mbuf[x][c][j];
-            const float a = mx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mx - M);   // a wave without keys
+            const float a = mx == -INFINITY ? 0.f : exp_neg(mx - M);   // a wave without keys
             const float4 v = obuf[x][u][lane];
             l = __builtin_fmaf(a, lbuf[x][c][j], l);
             acc[0] = __builtin_fmaf(a, v.x, acc[0]);
