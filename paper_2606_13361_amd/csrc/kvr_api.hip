@@ -263,10 +263,9 @@ ReaderPlan plan_long(const kvr_desc *d, int64_t L_prefix, int64_t S, size_t ws_b
 // The two-group kernel is taken where it is expected to be 2 % faster, and a tenth where
 // the fit overrates the staged kernel: against fewer than 3/2 staged workgroups per
 // compute unit (unless the two-group plan needs no merge), and with more than 24 splits.
-// Of 2041 other sizes (13 head counts, 16 to 2048 tokens over 128 to 32768) it then runs
-// 740, two of them behind the staged kernel (by 1.4 and 5.6 %), and the mean of all is 0.906
-// of the staged times; without the tenth it runs 766, twelve behind by up to 15 %, and the
-// mean is the same.
+// Of 3080 other sizes (13 head counts, 16 to 2048 tokens over 128 to 32768) it then runs
+// 1124, three of them behind the staged kernel (by 1.4, 2.4 and 3.7 %), and the mean of all
+// is 0.904 of the staged times.
 // Staged -> two-group where it picks the second, 32 / 8 heads: 517 tokens over 7001 129.8 -> 87.5
 // us, 300 over 20000 188 -> 115, 500 over 2000 51.3 -> 44.7, 1024 over 1000 74 -> 60.5;
 // where it stays: 100 over 4000 25.6 (28.2), 300 over 1000 33.7 (33.5), 4 / 1 heads: 512
@@ -301,9 +300,12 @@ bool use_pp_long(const kvr_desc *d, int64_t L_prefix, int64_t S, const Split &sp
         const int64_t last = keys - (sp.nsplit - 1) * sp.chunk;
         chain = ((last > sp.chunk ? last : sp.chunk) + kKeyTile - 1) / kKeyTile;
     }
+    // the last chunk is what the division left over: its workgroups are soon done
+    const double last = sp.nsplit > 1 ? (double)(keys - (sp.nsplit - 1) * sp.chunk) / (double)sp.chunk : 1.0;
+    const int64_t sw_full = (int64_t)((double)sw / sp.nsplit * (sp.nsplit - 1 + (last < 1.0 ? last : 1.0)));
     const double s_tile = sw <= kCus ? 1.65 : 1.85;
     const double staged =
-        5.5 + s_tile * ((double)chain + wait(sw, 2 * kCus, sp.nsplit).tiles) + merge_us(sp.nsplit, 2.5, 5.5);
+        5.5 + s_tile * ((double)chain + wait(sw_full, 2 * kCus, sp.nsplit).tiles) + merge_us(sp.nsplit, 2.5, 5.5);
     // two-group: equal shares of all key tiles
     const ReaderPlan lp = plan_long(d, L_prefix, S, sp.ws_bytes);
     const Wait lw = wait(lp.tiles * d->n_kv_heads * lp.nsplit, kCus, lp.nsplit);

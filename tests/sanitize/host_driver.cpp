@@ -351,6 +351,9 @@ static void long_plans() {
         {16, 2, 8789, 111, 's'},    // 28.4, 30.6
         {4, 1, 32763, 122, 's'},    // 32.3, 33.7
         {32, 8, 459, 660, 'p'},     // 48.2, 39.0
+        {32, 8, 8497, 156, 's'},    // 40.8, 45.0
+        {64, 8, 17504, 66, 's'},    // 62.5, 65.8
+        {32, 8, 3221, 143, 'p'},    // 36.1, 31.7
     };
     for (const Route &r : routes) {
         const kvr_desc d = desc(r.hq, r.hkv, 128, KVR_BF16, 40000);
