@@ -7,7 +7,7 @@
 // head; both groups (waves 0-3 and 4-7, one wave of each on every SIMD) hold the
 // same rows, group A runs the even 64-key tiles and group B the odd ones, and
 // the two (m, l, O) meet in LDS at the end.  The tile's steps are those of the
-// two-group kernel,
+// two-group kernel, written out again for this one's schedule and both head dims,
 //   GEMM(t)  O += V_{t-2} P_{t-2}  and  S_t = K_t Q^T
 //   SOFT(t)  mask, weights, reference maximum
 // one per barrier-separated phase, GEMM(t) in phase t and SOFT(t) in phase t + 1:

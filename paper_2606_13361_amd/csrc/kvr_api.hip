@@ -403,11 +403,12 @@ bool use_keys_split(const kvr_desc *d, int64_t n_prefix, int64_t n_tok, const Sp
 // cache (256 MB) by a repeated call.  A model's decode step reads every layer's cache
 // before it comes back to the first: from this many bytes on the hint pays there (36
 // layers: over 16391 rows 678 -> 623 us, 1000 rows 393 -> 369, 600 rows 329 -> 321;
-// over 512 rows, 2 MB a layer, 371 -> 378, over 256 269 -> 285), and costs one layer's
-// calls repeated on a cache that fits little (one token over 3774 rows 11.9 -> 12.1,
-// eight over 20000 18.7 -> 19.0; 24 over 32000, which don't fit, 39.0 -> 35.2).  The
-// row-split kernel (24 tokens over 16384 rows 23.6 -> 25.7) and the int8 artifact
-// (24 over 30001 32.3 -> 32.7) do without.
+// over 512 rows, 2 MB a layer, 371 -> 378, over 256 269 -> 285; 12 layers of four head
+// counts: 7 to 12 % from 100 MB in all on, else within 2 %, but 3.7 % behind where 12
+// layers' caches of one kv head, 8 MB each, all stay).  One layer's calls repeated on a cache
+// that stays there are behind: one token over 3774 rows 11.9 -> 12.1, eight over 20000
+// 18.7 -> 19.0, eight over 32000 26.2 -> 27.8.  The row-split kernel (24 tokens over 16384
+// rows 23.6 -> 25.7) and the int8 artifact (24 over 30001 32.3 -> 32.7) do without.
 constexpr int64_t kStreamBytes = 9 << 18;   // K and V rows of the prefix, all kv heads
 
 // Whether the attention kernel of a continuation rotates its rows itself.
