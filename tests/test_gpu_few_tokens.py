@@ -1,7 +1,7 @@
-"""The decoder layer over a few tokens (2 .. 48), whose products are this
+"""The decoder layer over a few tokens (2 .. 48, and one), whose products are this
 library's kernels: token counts on both sides of a group of eight and of a
-16-token tile, the three hidden widths, output widths that leave ragged tiles,
-both element types.  Against the fp64 layer oracle with every held tensor
+16-token tile, the three hidden widths, output widths that leave ragged tiles or
+give a workgroup several, short and long prefixes, both element types.  Against the fp64 layer oracle with every held tensor
 rounded, at the layer tests' bars (|d| <= 2^-6 |x| + 2e-2 and a normalized rms
 of 2^-7 in bf16; fp16 keeps three more bits: a quarter of them)."""
 import numpy as np
@@ -25,7 +25,14 @@ def np64(t):
 # (hidden, intermediate, Hq, Hkv, d, L_prefix, tokens, dtype)
 CASES = [(2048, 512, 8, 2, 128, 33, 2, BF16), (2048, 576, 4, 4, 64, 0, 8, BF16), (2560, 640, 8, 2, 128, 70, 9, BF16),
          (2560, 320, 8, 2, 128, 10, 16, F16), (2560, 1088, 4, 1, 128, 100, 17, BF16), (4096, 192, 8, 2, 128, 64, 24, BF16),
-         (4096, 256, 4, 2, 64, 40, 25, F16), (2048, 320, 8, 2, 128, 5, 33, BF16), (2560, 448, 8, 8, 128, 20, 48, BF16)]
+         (4096, 256, 4, 2, 64, 40, 25, F16), (2048, 320, 8, 2, 128, 5, 33, BF16), (2560, 448, 8, 8, 128, 20, 48, BF16),
+         # several tiles a workgroup, a ragged last round: more than 2048 gate rows, more than 4096 q|k|v outputs
+         (2560, 4160, 32, 4, 128, 40, 17, BF16), (2048, 4160, 32, 4, 128, 33, 24, F16), (4096, 4160, 32, 4, 128, 20, 48, BF16),
+         (2048, 2112, 32, 4, 128, 10, 33, BF16), (4096, 2112, 32, 8, 128, 5, 16, F16), (2560, 4160, 32, 4, 128, 70, 40, F16),
+         (4096, 6208, 32, 8, 128, 16, 5, BF16), (2048, 4160, 32, 4, 128, 3, 8, BF16), (2560, 6208, 32, 8, 128, 9, 35, BF16),
+         # one and eight tokens over many key splits, the last of which stores the rows
+         (2560, 320, 32, 8, 128, 5000, 1, BF16), (2560, 320, 32, 8, 128, 4001, 1, F16), (2048, 512, 8, 2, 128, 3001, 8, BF16),
+         (2560, 320, 32, 8, 128, 5000, 8, F16)]
 
 
 @pytest.mark.parametrize("H,I,Hq,Hkv,d,Lp,T,dt", CASES)
